@@ -575,6 +575,21 @@ __global__ __launch_bounds__(kThreads) void k_lscv_prep(const ColDesc* __restric
 // lane's sample, for the HC bandwidths.  FIRST: the run's first pair starts
 // the plain sums (S1 = e, S2 = e e instead of adding them to zero: the same
 // values, as e is never -0), which saves clearing 2 HC registers per run.
+//
+// Bound: vector issue.  On gfx950 v_exp_f32 holds a SIMD's vector issue for
+// 8.1 cycles a wave; the plain FP32 instructions of two waves issue together
+// (2.0 to 2.5 cycles each instead of 4.2) as long as both waves are between
+// their exponentials.  So the terms go in groups of kExpGroup: their
+// products, their exponentials back to back at raised priority (a wave
+// leaves its exponentials behind quickly), then their sums, 2 kExpGroup + the
+// next products of plain work in one stretch that other waves' plain work
+// pairs with.  Cycles a term and SIMD, n = 1e5 x 256 bandwidths, HC = 16: one
+// term at a time with its priority raised from the exponential to its sums
+// 16.9; groups of 2 15.1; of 4 14.96; of 8 15.1; the same groups without
+// raised priority 21.2, with the plain part raised instead 21.0.  Sum of the
+// parts: 8.1 + 3.125 plain at 2.0 + the runs' folds (0.27) = 14.6.  A column
+// of n = 1e5, 256 bandwidths: 138.2 -> 121.9 ms (9.26 -> 10.50e12 terms/s),
+// every sum bitwise unchanged.
 template <int HC, bool MASK, bool FIRST>
 __device__ __forceinline__ void lscv_quad(const float4 v, int jg, float xi, int i, const float (&ck)[HC],
                                           float (&r1)[HC], float (&r2)[HC]) {
@@ -584,29 +599,22 @@ __device__ __forceinline__ void lscv_quad(const float4 v, int jg, float xi, int 
     const float d = xi - xs[u];
     float t = d * d;
     if (MASK) t = (jg + u > i) ? t : kInfF;
-    // One term at a time, in program order: mul, exp2, then its two
-    // consumers.  A wave then holds one exponential in flight and waits on
-    // it while the SIMD's other waves issue plain instructions; measured on
-    // gfx950 this overlaps more of the transcendental unit's time than
-    // exponentials issued back to back (the compiler's own order, which
-    // also pairs them at pair boundaries): +1% at HC = 16, +13% at HC = 8.
-    // The wave raises its issue priority from the exponential until both
-    // consumers have issued, so that a wave whose exponential has completed
-    // goes ahead of waves starting a new term: +8% at HC = 16, +10% at
-    // HC = 8.  The barrier and the priority only fix the order of issue;
-    // the arithmetic and the summation order are unchanged.
 #pragma unroll
-    for (int k = 0; k < HC; ++k) {
-      __builtin_amdgcn_s_setprio(1);
-      const float e = __builtin_amdgcn_exp2f(t * ck[k]);
-      if (FIRST && u == 0) {
-        r1[k] = e;
-        r2[k] = e * e;
-      } else {
-        r1[k] += e;
-        r2[k] = __builtin_fmaf(e, e, r2[k]);
+    for (int k0 = 0; k0 < HC; k0 += kExpGroup) {
+      float e[kExpGroup];
+#pragma unroll
+      for (int k = 0; k < kExpGroup; ++k) e[k] = t * ck[k0 + k];
+      exp2_group(e);
+#pragma unroll
+      for (int k = 0; k < kExpGroup; ++k) {
+        if (FIRST && u == 0) {
+          r1[k0 + k] = e[k];
+          r2[k0 + k] = e[k] * e[k];
+        } else {
+          r1[k0 + k] += e[k];
+          r2[k0 + k] = __builtin_fmaf(e[k], e[k], r2[k0 + k]);
+        }
       }
-      __builtin_amdgcn_s_setprio(0);
       __builtin_amdgcn_sched_barrier(0);
     }
   }

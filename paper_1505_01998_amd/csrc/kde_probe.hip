@@ -61,7 +61,8 @@ __global__ __launch_bounds__(kProbeThreads) void k_issue(float a, float b, int i
 // fma per term), then the next distance t + dt (one add per 16 terms).  With
 // t0 = dt = 0 every exponential is of zero.  Each term is issued in program
 // order behind a scheduling barrier, with the wave's priority raised from the
-// exponential to its consumers, as in the LSCV sweep's inner loop.
+// exponential to its consumers (the LSCV sweep itself groups its terms, which
+// is faster).
 __global__ __launch_bounds__(kProbeThreads) void k_issue_mix(float t0, float dt, float c0, int iters,
                                                              float* __restrict__ out) {
   constexpr int HC = 16;
