@@ -390,6 +390,13 @@ __global__ void k_plugin_final(const ColDesc* __restrict__ cols, const int* __re
 // exponential is exactly 0 and whose He_r is finite.  CLAMP (padded tiles,
 // or a column whose scaled range could overflow He_r): w = min(w, kWMax),
 // so an infinite or huge distance also gives exactly 0.
+// Bound: vector issue, as the LSCV sweep (see lscv_quad); the pairs of one
+// LDS read go together: their exponentials at raised priority, then their
+// polynomials and sums in pair order, which the plain work of other waves
+// pairs with.  At n = 5e5 against one pair at a time: r = 8 24.8 -> 23.6 ms,
+// r = 6 21.8 -> 20.5, r = 4 19.5 -> 18.8 (29.7, 25.8, 23.6 cycles a pair;
+// 8.1 for the exponential and 2.4 for each of 9, 8, 7 plain instructions),
+// the sums bitwise unchanged.
 template <int R, bool MASK, bool CLAMP>
 __device__ __forceinline__ void psi_run(const float4* __restrict__ tile, int jl, int jg, float yi, int i, float& aS,
                                         float& cS, float& aA, float& cA) {
@@ -398,21 +405,23 @@ __device__ __forceinline__ void psi_run(const float4* __restrict__ tile, int jl,
   for (int q = 0; q < kRun / 4; ++q) {
     const float4 v = tile[(jl >> 2) + q];
     const float ys[4] = {v.x, v.y, v.z, v.w};
+    float w[4], e[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const float d = yi - ys[u];
-      float w = d * d;
-      if (CLAMP) w = fminf(w, kWMax);
-      if (MASK) w = (jg + 4 * q + u > i) ? w : kWMax;
-      // issue priority raised from the exponential to its two consumers,
-      // as in the LSCV sweep (order of issue only; +29% on this pass)
-      __builtin_amdgcn_s_setprio(1);
-      const float e = __builtin_amdgcn_exp2f(w * kPsiExp2);
-      const float hw = herm_w<R>(w);
-      rs = __builtin_fmaf(hw, e, rs);
-      ra = __builtin_fmaf(fabsf(hw), e, ra);
-      __builtin_amdgcn_s_setprio(0);
+      w[u] = d * d;
+      if (CLAMP) w[u] = fminf(w[u], kWMax);
+      if (MASK) w[u] = (jg + 4 * q + u > i) ? w[u] : kWMax;
+      e[u] = w[u] * kPsiExp2;
     }
+    exp2_group(e);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float hw = herm_w<R>(w[u]);
+      rs = __builtin_fmaf(hw, e[u], rs);
+      ra = __builtin_fmaf(fabsf(hw), e[u], ra);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
   kahan_add(aS, cS, rs);
   kahan_add(aA, cA, ra);
