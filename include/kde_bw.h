@@ -434,8 +434,9 @@ kde_status kde_request_footprint(const kde_ctx* ctx, const kde_request* req, uin
  * [j_begin[k], j_end[k]) with j > i, holds pairs[k] such pairs, and the items
  * are ordered longest first.  seg: j-range per item as the "seg" option
  * (0 = whole rows, > 0 rounded up to a multiple of 512, < 0 = automatic under
- * the default launch size, lengthened when the pass would exceed 2^24 work
- * units).  Writes min(cap, count) items and sets *n_items = count.
+ * the default launch size, shortened when the pass would hold too few work
+ * units to fill the device, lengthened when it would exceed 2^24; the shortest
+ * items of small passes are summed in up to 8 pieces).  Writes min(cap, count) items and sets *n_items = count.
  * Host-only.  KDE_E_INVAL for n outside [2, KDE_MAX_N], n_h outside
  * [0, KDE_MAX_NH], cap < 0, or NULL arrays with cap > 0. */
 kde_status kde_plan_items(int64_t n, int32_t n_h, int64_t seg, int32_t cap, int32_t* n_items, int32_t* row_begin,

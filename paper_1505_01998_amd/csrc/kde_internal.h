@@ -11,6 +11,11 @@ namespace kde {
 // owns one "row" of kBI consecutive samples i (one per lane).
 constexpr int kThreads = 256;
 constexpr int kBI = kThreads;
+// Threads per block of the psi kernels of smaller columns: 16 waves share the
+// runs of 64 samples i.  A work item's row of kBI samples is kPsiGroups such
+// units.
+constexpr int kPsiThreads = 1024;
+constexpr int kPsiGroups = kBI / 64;
 // j-tile staged in LDS per step; item j-ranges are whole multiples of it.
 constexpr int kBJ = 512;
 // Every column is padded with +inf up to at least n + kPad so that every
@@ -62,6 +67,68 @@ __device__ __forceinline__ double exp_cw(double x) {
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
   return ldexp(p, (int)k);
+}
+
+// ---- sums over the 64 lanes of a wave, all lanes active, in vector registers
+// (row permutes and lane swaps; no LDS traffic).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Each row of 16 lanes: every lane gets its row's sum.
+__device__ __forceinline__ double row16_sum(double v) {
+  v += dpp_f64<0xB1>(v);   // lane ^ 1
+  v += dpp_f64<0x4E>(v);   // lane ^ 2
+  v += dpp_f64<0x141>(v);  // the other half of 8
+  v += dpp_f64<0x140>(v);  // the other half of 16
+  return v;
+}
+
+// a + b with the upper half of a exchanged for the lower half of b: lanes
+// 0 - 31 get a[l] + a[l + 32], lanes 32 - 63 get b[l - 32] + b[l].
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)ua, (uint32_t)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+  return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+         __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// The same between neighbouring rows of 16: rows 0 and 2 get a's two rows
+// added, rows 1 and 3 b's.
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
+  return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+         __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// Sums of N values over the wave's lanes into out[0 .. N) (N a multiple of
+// 4): two exchange steps leave N / 4 values a lane, row r of 16 lanes holding
+// values r N / 4 and up, and the rows are summed in place.  3 N / 2 exchanges
+// and sums plus 3 N row steps against 18 N LDS permutes and sums of a full
+// butterfly per value; the order of every sum does not depend on N.
+template <int N>
+__device__ __forceinline__ void wave_sums(const double (&v)[N], double* out, int lane) {
+  double h[N / 2];
+#pragma unroll
+  for (int k = 0; k < N / 2; ++k) h[k] = swap32_add(v[k], v[k + N / 2]);
+#pragma unroll
+  for (int k = 0; k < N / 4; ++k) {
+    const double s = row16_sum(swap16_add(h[k], h[k + N / 4]));
+    if ((lane & 15) == 0) out[(lane >> 4) * (N / 4) + k] = s;
+  }
+}
+
+// Two values: lane 0 gets the sum of a, lane 32 the sum of b.
+__device__ __forceinline__ double wave_sum2(double a, double b) {
+  const double s = swap32_add(a, b);
+  return row16_sum(swap16_add(s, s));
 }
 
 // Exponentials issued together in the FP32 pair loops (2: 1% slower in the
@@ -144,17 +211,19 @@ struct ColDesc {
   int raw_f64;
   int n_h;              // LSCV grid points (0: no LSCV for this column)
   int n_chunks;         // ceil(n_h / HC)
-  int n_items;          // LSCV work items
-  int n_items_psi;      // psi work items
+  int n_items;          // LSCV partial-sum slots a bandwidth (work items x pieces)
+  int n_items_psi;      // psi partial-sum slots (work items x psi_groups)
   int grid_kind;        // kGridExplicit / kGridPaper / kGridLogRot
   int pad0;
   double grid_lo, grid_hi;
 };
 
-// One block of a pair kernel: the samples i in [row*kBI, row*kBI + kBI) of
-// column `col` against j in [j_begin, j_end) (a multiple of kBJ long; a
-// column's last item may run past n into the +inf padding).  `item` is the
-// item's index within its column, `chunk` the bandwidth chunk (LSCV).
+// One block of a pair kernel: the samples i in [row*kBI, row*kBI + kBI) (psi
+// with chunk 1: [row*64, row*64 + 64)) of column `col` against j in [j_begin, j_end) (a multiple of 64 long; a
+// column's last unit may run past n into the +inf padding).  `item` is the
+// partial-sum slot within the column (its work item, times the units an item
+// is cut into, plus the unit), `chunk` the bandwidth chunk (LSCV)
+// or the psi geometry (0: rows of kBI samples, 1: of 64).
 struct Unit {
   int col, row, j_begin, j_end, item, chunk;
 };
@@ -178,9 +247,9 @@ void launch_psi_finish(hipStream_t s, const ColDesc* cols, const int* ids, int n
 void launch_plugin_final(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids);
 void launch_lscv_prep(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int hc);
 void launch_lscv_finalize(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int f64);
-// Pair kernels act on units[u0 .. u0 + n_units).
-void launch_psi_units(hipStream_t s, int r, int f64, int conditional, const ColDesc* cols, const Unit* units, int u0,
-                      int n_units);
+// Pair kernels act on units[u0 .. u0 + n_units).  wide: units of 64 samples i.
+void launch_psi_units(hipStream_t s, int r, int f64, int conditional, int wide, const ColDesc* cols,
+                      const Unit* units, int u0, int n_units);
 // mfma: use the matrix-core variant (FP32, 16 bandwidths per unit only).
 // Tile pruning: per column, the cut distance of every bandwidth chunk from
 // the near-tile sums (relative bound eps on every skipped share).

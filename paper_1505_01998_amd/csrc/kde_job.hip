@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
 #include <vector>
 
 #include "kde_runtime.h"
@@ -26,6 +27,9 @@
 struct kde_job {
   kde_ctx* c = nullptr;
   kde::ColPlan plan;
+  // the LSCV cut by launch size alone, when it differs: checkpoints written
+  // under it resume under it
+  std::unique_ptr<kde::ColPlan> earlier;
   char* block = nullptr;
   kde::DevState* st = nullptr;  // device state of the column
   kde::DevState h_st{};
@@ -61,6 +65,37 @@ constexpr char kMagic[8] = {'K', 'D', 'E', 'J', 'O', 'B', '\0', '\0'};
 constexpr int32_t kVersion = 2;
 
 bool serving(const kde_ctx* c) { return c->server && kde::server_running(c->server.get()); }
+
+// Partial-sum slots of a plan (the header's items_psi, items_lscv).
+int64_t psi_slots(const kde::ColPlan& p) { return (int64_t)p.psi_items.pairs.size() * p.psi_groups; }
+int64_t lscv_slots(const kde::ColPlan& p) { return (int64_t)p.lscv_items.pairs.size() * p.lscv_pieces; }
+
+bool cut_of(const JobHeader& h, const kde::ColPlan& p) {
+  return h.items_psi == psi_slots(p) && h.items_lscv == lscv_slots(p) && h.block_bytes == (int64_t)p.bytes;
+}
+
+// Older checkpoints hold one psi slot an item where a plan has psi_groups:
+// their block is this much shorter from the psi slots on.
+size_t psi_gap(const kde::ColPlan& p) {
+  const size_t items = p.psi_items.pairs.size();
+  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+  return p.plugin ? al(16 * items * p.psi_groups) - al(16 * items) : 0;
+}
+
+bool older_cut_of(const JobHeader& h, const kde::ColPlan& p) {
+  return h.items_psi == (int64_t)p.psi_items.pairs.size() && h.items_lscv == lscv_slots(p) &&
+         h.block_bytes == (int64_t)(p.bytes - psi_gap(p));
+}
+
+void make_units(kde_job* j) {
+  j->psi_u.clear();
+  j->psi_c.clear();
+  j->lscv_u.clear();
+  j->lscv_c.clear();
+  kde::psi_units_of(j->plan, 0, j->psi_u, j->psi_c);
+  // with tile pruning the sweep units name the pruned-sweep descriptor (2)
+  kde::lscv_units_of(j->plan, j->plan.prune ? 2 : 0, j->lscv_u, j->lscv_c);
+}
 
 uint64_t ckpt_bytes(const kde_job* j) {
   return sizeof(JobHeader) + (uint64_t)j->plan.bytes + 16 * (uint64_t)j->plan.n_h;
@@ -103,6 +138,9 @@ kde_status kde_job_create(kde_ctx* c, const kde_request* req, kde_job** out) {
   std::string e = kde::plan_column(c, r, j->plan);
   if (!e.empty()) return fail(c, KDE_E_INVAL, e);
   kde::ColPlan& p = j->plan;
+  std::unique_ptr<kde::ColPlan> earlier(new kde::ColPlan());
+  (void)kde::plan_column(c, r, *earlier, false);
+  if (lscv_slots(p) != lscv_slots(*earlier)) j->earlier = std::move(earlier);
   if (hipMalloc((void**)&j->block, p.bytes) != hipSuccess) {
     j->block = nullptr;
     return fail(c, KDE_E_NOMEM, "device allocation of the job's block failed");
@@ -125,9 +163,7 @@ kde_status kde_job_create(kde_ctx* c, const kde_request* req, kde_job** out) {
     (void)hipFree(j->st);
     return s;
   }
-  kde::psi_units_of(p, 0, j->psi_u, j->psi_c);
-  // with tile pruning the sweep units name the pruned-sweep descriptor (2)
-  kde::lscv_units_of(p, p.prune ? 2 : 0, j->lscv_u, j->lscv_c);
+  make_units(j.get());
   j->stage = p.stages == 3 ? 0 : 1;
   for (const kde::UnitCost& u : j->psi_c) j->total += u.evals * (3 - j->stage);
   for (const kde::UnitCost& u : j->lscv_c) j->total += u.evals;
@@ -291,8 +327,8 @@ kde_status kde_job_checkpoint(kde_job* j, void* buf, uint64_t bytes) {
   h.prec = j->prec;
   h.grid_kind = p.grid_kind;
   h.prune = p.prune;
-  h.items_psi = (int64_t)p.psi_items.pairs.size();
-  h.items_lscv = (int64_t)p.lscv_items.pairs.size();
+  h.items_psi = psi_slots(p);
+  h.items_lscv = lscv_slots(p);
   h.block_bytes = (int64_t)p.bytes;
   h.stats_done = j->stats_done;
   h.plugin_done = j->plugin_done;
@@ -325,23 +361,44 @@ kde_status kde_job_resume(kde_job* j, const void* buf, uint64_t bytes) {
   if (bytes < sizeof(JobHeader)) return fail(c, KDE_E_INVAL, "checkpoint too short");
   JobHeader h;
   std::memcpy(&h, buf, sizeof(h));
-  const kde::ColPlan& p = j->plan;
+  // a checkpoint of this cut, or of the earlier LSCV cut; in an older one
+  // (psi slots one an item) a plug-in stage that it interrupts starts again
+  const kde::ColPlan& p = cut_of(h, j->plan) || !j->earlier ? j->plan : *j->earlier;
+  const bool older = !cut_of(h, p) && older_cut_of(h, p);
+  const size_t gap = older ? psi_gap(p) : 0;
   const bool same = std::memcmp(h.magic, kMagic, sizeof(kMagic)) == 0 && h.version == kVersion && h.n == p.n &&
                     h.f64 == p.f64 && h.plugin == (int)p.plugin && h.lscv == (int)p.lscv && h.stages == p.stages &&
                     h.n_h == p.n_h && h.hc == j->hc && h.mfma == j->mfma && h.cond == j->cond &&
                     h.prec == j->prec && h.grid_kind == p.grid_kind && h.prune == (int)p.prune &&
-                    h.items_psi == (int64_t)p.psi_items.pairs.size() &&
-                    h.items_lscv == (int64_t)p.lscv_items.pairs.size() && h.block_bytes == (int64_t)p.bytes;
+                    (older || cut_of(h, p));
   if (!same)
     return fail(c, KDE_E_INVAL,
                 "checkpoint does not belong to this request shape, precision and options (or is not a checkpoint)");
-  if (bytes < ckpt_bytes(j)) return fail(c, KDE_E_INVAL, "checkpoint truncated");
-  if (h.stage < 0 || h.stage > 3 || h.psi_next < 0 || h.psi_next > (int64_t)j->psi_u.size() || h.lscv_next < 0 ||
-      h.lscv_next > (int64_t)j->lscv_u.size())
+  if (bytes < sizeof(JobHeader) + (uint64_t)h.block_bytes + 16 * (uint64_t)p.n_h)
+    return fail(c, KDE_E_INVAL, "checkpoint truncated");
+  if (h.stage < 0 || h.stage > 3 || h.psi_next < 0 || h.psi_next > h.items_psi || h.lscv_next < 0 ||
+      h.lscv_next > lscv_slots(p) * p.n_chunks)
     return fail(c, KDE_E_INVAL, "checkpoint cursor out of range");
   if (hipSetDevice(c->device) != hipSuccess) return fail(c, KDE_E_DEVICE, "hipSetDevice failed");
+  if (&p != &j->plan) {
+    char* block = nullptr;
+    if (hipMalloc((void**)&block, p.bytes) != hipSuccess)
+      return fail(c, KDE_E_NOMEM, "device allocation of the job's block failed");
+    (void)hipFree(j->block);
+    j->block = block;
+    std::swap(j->plan, *j->earlier);  // p now names the plan before it: j->plan below
+    make_units(j);
+  }
+  const kde::ColPlan& jp = j->plan;
+  if (older)
+    for (int64_t k = 0; k < h.psi_next; ++k) h.remaining += jp.psi_items.pairs[(size_t)k];
+  if (older) h.psi_next = 0;
   const char* in = (const char*)buf;
-  KDE_HIP_TRY(c, hipMemcpy(j->block, in + sizeof(JobHeader), p.bytes, hipMemcpyHostToDevice));
+  const size_t head = gap ? jp.off_psi_part : jp.bytes;  // gap: the psi slots themselves are not kept
+  KDE_HIP_TRY(c, hipMemcpy(j->block, in + sizeof(JobHeader), head, hipMemcpyHostToDevice));
+  if (gap)
+    KDE_HIP_TRY(c, hipMemcpy(j->block + jp.off_psi_sums, in + sizeof(JobHeader) + jp.off_psi_sums - gap,
+                             jp.bytes - jp.off_psi_sums, hipMemcpyHostToDevice));
   KDE_HIP_TRY(c, hipMemcpy(j->st, &h.st, sizeof(kde::DevState), hipMemcpyHostToDevice));
   j->h_st = h.st;
   j->stats_done = h.stats_done;
@@ -358,10 +415,11 @@ kde_status kde_job_resume(kde_job* j, const void* buf, uint64_t bytes) {
   if (j->done) {
     j->res = h.res;
     j->res.g_out = j->res.gscale_out = nullptr;
-    const double* tail = (const double*)(in + sizeof(JobHeader) + p.bytes);
-    if (p.lscv) {
-      j->g.assign(tail, tail + p.n_h);
-      j->gs.assign(tail + p.n_h, tail + 2 * p.n_h);
+    const double* tail = (const double*)(in + sizeof(JobHeader) + h.block_bytes);
+    if (jp.lscv) {
+      const int n_h = jp.n_h;
+      j->g.assign(tail, tail + n_h);
+      j->gs.assign(tail + n_h, tail + 2 * n_h);
     }
   }
   return KDE_OK;

@@ -379,6 +379,10 @@ __global__ void k_plugin_final(const ColDesc* __restrict__ cols, const int* __re
   d.h_plugin = pow(rad, 0.2);
 }
 
+// Where a unit's sweep ends: its j-range, cut to the runs of kRun that hold a
+// sample (what lies beyond n is padding and adds exact zeros).
+__device__ __forceinline__ int unit_end(const Unit& u, int n) { return min(u.j_end, (n + kRun - 1) / kRun * kRun); }
+
 // ------------------------------------------------------------------ psi pair kernels
 // Mixed form.  The samples are pre-scaled by 1/g (y = x / g, one O(n) pass
 // per stage), so a pair's w = u^2 = (y_i - y_j)^2 needs no per-pair scaling;
@@ -398,12 +402,11 @@ __global__ void k_plugin_final(const ColDesc* __restrict__ cols, const int* __re
 // 8.1 for the exponential and 2.4 for each of 9, 8, 7 plain instructions),
 // the sums bitwise unchanged.
 template <int R, bool MASK, bool CLAMP>
-__device__ __forceinline__ void psi_run(const float4* __restrict__ tile, int jl, int jg, float yi, int i, float& aS,
-                                        float& cS, float& aA, float& cA) {
-  float rs = 0.f, ra = 0.f;
+__device__ __forceinline__ void psi_run(const float4* __restrict__ run, int jg, float yi, int i, float& rs, float& ra) {
+  rs = ra = 0.f;
 #pragma unroll 4
   for (int q = 0; q < kRun / 4; ++q) {
-    const float4 v = tile[(jl >> 2) + q];
+    const float4 v = run[q];
     const float ys[4] = {v.x, v.y, v.z, v.w};
     float w[4], e[4];
 #pragma unroll
@@ -423,11 +426,10 @@ __device__ __forceinline__ void psi_run(const float4* __restrict__ tile, int jl,
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  kahan_add(aS, cS, rs);
-  kahan_add(aA, cA, ra);
 }
 
-
+// A psi unit of a large column: a row of 256 samples i, one per lane, against
+// the unit's j-range.
 template <int R>
 __global__ __launch_bounds__(kThreads) void k_psi_units_f32(const ColDesc* __restrict__ cols,
                                                             const Unit* __restrict__ units, int u0) {
@@ -445,49 +447,128 @@ __global__ __launch_bounds__(kThreads) void k_psi_units_f32(const ColDesc* __res
   const int i = row0 + tid;
   const float yi = (i < n) ? y[i] : 0.f;
   const int wave_i0 = row0 + wave * 64;
-  float aS = 0.f, cS = 0.f, aA = 0.f, cA = 0.f;
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+  float aS = 0.f, cS = 0.f, aA = 0.f, cA = 0.f, rs, ra;
+  const int j_end = unit_end(u, n);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
-    for (int q = tid; q < kBJ / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(y + t0)[q];
+    for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(y + t0)[q];
     __syncthreads();
     int js = max(t0, wave_i0);
-    const int te = t0 + kBJ;
     if (js < te) {
-      const bool clamp = !fast || te > n;  // uniform: padded tile or unsafe range
+      // uniform: unsafe range, or the tile holds padding (the two forms round
+      // their polynomials differently, so the choice goes by whole tiles)
+      const bool clamp = !fast || t0 + kBJ > n;
       if (js == wave_i0) {
         if (clamp)
-          psi_run<R, true, true>(tile, js - t0, js, yi, i, aS, cS, aA, cA);
+          psi_run<R, true, true>(tile + (js - t0) / 4, js, yi, i, rs, ra);
         else
-          psi_run<R, true, false>(tile, js - t0, js, yi, i, aS, cS, aA, cA);
+          psi_run<R, true, false>(tile + (js - t0) / 4, js, yi, i, rs, ra);
+        kahan_add(aS, cS, rs);
+        kahan_add(aA, cA, ra);
         js += kRun;
       }
-      if (clamp) {
-        for (; js < te; js += kRun) psi_run<R, false, true>(tile, js - t0, js, yi, i, aS, cS, aA, cA);
-      } else {
-        for (; js < te; js += kRun) psi_run<R, false, false>(tile, js - t0, js, yi, i, aS, cS, aA, cA);
+      for (; js < te; js += kRun) {
+        if (clamp)
+          psi_run<R, false, true>(tile + (js - t0) / 4, js, yi, i, rs, ra);
+        else
+          psi_run<R, false, false>(tile + (js - t0) / 4, js, yi, i, rs, ra);
+        kahan_add(aS, cS, rs);
+        kahan_add(aA, cA, ra);
       }
     }
   }
   const bool valid = i < n;
-  double vs = valid ? (double)aS - (double)cS : 0.0;
-  double va = valid ? (double)aA - (double)cA : 0.0;
-  vs = wave_sum(vs);
-  va = wave_sum(va);
-  if (lane == 0) {
-    red[0][wave] = vs;
-    red[1][wave] = va;
-  }
+  const double v = wave_sum2(valid ? (double)aS - (double)cS : 0.0, valid ? (double)aA - (double)cA : 0.0);
+  if ((lane & 31) == 0) red[lane >> 5][wave] = v;
   __syncthreads();
   if (tid < 2)
     c.psi_part[(int64_t)tid * c.n_items_psi + u.item] = ((red[tid][0] + red[tid][1]) + red[tid][2]) + red[tid][3];
 }
 
+// A psi unit of a smaller column: 64 samples i (one per lane of every wave)
+// against the unit's j-range, by the 16 waves of a block.  A tile holds
+// 16 runs of 64 j, one a wave; the waves leave their runs' sums in LDS and
+// waves 0 and 1 fold them, run by run in ascending j, into the lane's
+// compensated sums of He e and |He| e while the next tile is swept.  The
+// folds are those of one wave walking the whole j-range, as in the kernel
+// above, so the two agree bitwise a lane; a j-range cut into more units would
+// not do (the compensated sum depends on its grouping: psi moved by up to
+// 4e-8 at kappa = 1000).  Bound: vector issue (psi_run).  With 256 samples i
+// a block a column of n = 1000 had 4 blocks of 4 waves, one of n = 1e5 3
+// waves a SIMD and a long last round.  A stage of r = 6 at n = 1000 36 -> 7
+// us, at n = 12345 350 -> 47 us, at n = 1e5 1297 -> 977 us; eight waves a
+// block take a call 2% longer at n = 5e3 to 1.2e4, four 14%; at n = 5e5 the
+// 256-sample kernel is 4% faster (a barrier every 512 j against 64 j a wave).
+constexpr int kPsiWaves = kPsiThreads / 64;
+constexpr int kPsiTile = kPsiWaves * kRun;
+
+template <int R>
+__global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_psi_wide_f32(
+    const ColDesc* __restrict__ cols, const Unit* __restrict__ units, int u0) {
+  const Unit u = units[u0 + blockIdx.x];
+  const ColDesc c = cols[u.col];
+  if (!c.st->active) return;
+  const float* y = c.y32;
+  const int n = c.n;
+  const bool fast = c.st->psi_fast != 0;
+  __shared__ __attribute__((aligned(16))) float tile[2][kPsiTile];
+  __shared__ float part[2][2][kPsiWaves][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i0 = u.row * 64;
+  const int i = i0 + lane;
+  const float yi = (i < n) ? y[i] : 0.f;
+  const int j_begin = max(u.j_begin, i0), j_end = unit_end(u, n);
+  float acc = 0.f, comp = 0.f;  // waves 0 and 1: the lane's folded sums
+  if (j_begin + tid < j_end) tile[0][tid] = y[j_begin + tid];
+  __syncthreads();
+  for (int t0 = j_begin, b = 0; t0 < j_end; t0 += kPsiTile, b ^= 1) {
+    const int jn = t0 + kPsiTile + tid;
+    float next = 0.f;
+    if (jn < j_end) next = y[jn];
+    const int js = t0 + wave * kRun;
+    if (js < j_end) {
+      const float4* run = reinterpret_cast<const float4*>(&tile[b][wave * kRun]);
+      // the kBJ tile that the kernel above would hold the run in
+      const bool clamp = !fast || js - ((js - u.j_begin) & (kBJ - 1)) + kBJ > n;
+      float rs, ra;
+      if (js == i0) {
+        if (clamp)
+          psi_run<R, true, true>(run, js, yi, i, rs, ra);
+        else
+          psi_run<R, true, false>(run, js, yi, i, rs, ra);
+      } else {
+        if (clamp)
+          psi_run<R, false, true>(run, js, yi, i, rs, ra);
+        else
+          psi_run<R, false, false>(run, js, yi, i, rs, ra);
+      }
+      part[b][0][wave][lane] = rs;
+      part[b][1][wave][lane] = ra;
+    }
+    tile[b ^ 1][tid] = next;
+    __syncthreads();
+    if (wave < 2) {
+      // read before the buffer's next use: the wave reaches the next barrier
+      // only after these reads
+      const int runs = min(kPsiWaves, (j_end - t0) / kRun);
+      for (int r = 0; r < runs; ++r) kahan_add(acc, comp, part[b][wave][r][lane]);
+    }
+  }
+  if (wave < 2) {
+    const double v = (i < n) ? (double)acc - (double)comp : 0.0;
+    const double s = wave_sum2(v, v);
+    if (lane == 0) c.psi_part[(int64_t)wave * c.n_items_psi + u.item] = s;
+  }
+}
+
 template <int R, bool MASK>
-__device__ __forceinline__ void psi_run64(const double* __restrict__ tile, int jl, int jg, double xi, int i,
+__device__ __forceinline__ void psi_run64(const double* __restrict__ run, int jg, double xi, int i,
                                           double ig2, double cg, double& s, double& a) {
 #pragma unroll 4
   for (int q = 0; q < kRun; ++q) {
-    const double d = xi - tile[jl + q];
+    const double d = xi - run[q];
     double t = d * d;
     if (MASK) t = (jg + q > i) ? t : kInfD;
     const double w = fmin(t * ig2, (double)kWMax);
@@ -518,31 +599,75 @@ __global__ __launch_bounds__(kThreads) void k_psi_units_f64(const ColDesc* __res
   const int wave_i0 = row0 + wave * 64;
   const double ig2 = c.st->cd[0], cg = c.st->cd[1];
   double s = 0.0, a = 0.0;
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+  const int j_end = unit_end(u, n);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
-    for (int q = tid; q < kBJ / 2; q += kThreads)
+    for (int q = tid; q < (te - t0) / 2; q += kThreads)
       reinterpret_cast<double2*>(tile)[q] = reinterpret_cast<const double2*>(x + t0)[q];
     __syncthreads();
     int js = max(t0, wave_i0);
-    const int te = t0 + kBJ;
     if (js < te) {
       if (js == wave_i0) {
-        psi_run64<R, true>(tile, js - t0, js, xi, i, ig2, cg, s, a);
+        psi_run64<R, true>(tile + js - t0, js, xi, i, ig2, cg, s, a);
         js += kRun;
       }
-      for (; js < te; js += kRun) psi_run64<R, false>(tile, js - t0, js, xi, i, ig2, cg, s, a);
+      for (; js < te; js += kRun) psi_run64<R, false>(tile + js - t0, js, xi, i, ig2, cg, s, a);
     }
   }
   const bool valid = i < n;
-  double vs = wave_sum(valid ? s : 0.0);
-  double va = wave_sum(valid ? a : 0.0);
-  if (lane == 0) {
-    red[0][wave] = vs;
-    red[1][wave] = va;
-  }
+  const double v = wave_sum2(valid ? s : 0.0, valid ? a : 0.0);
+  if ((lane & 31) == 0) red[lane >> 5][wave] = v;
   __syncthreads();
   if (tid < 2)
     c.psi_part[(int64_t)tid * c.n_items_psi + u.item] = ((red[tid][0] + red[tid][1]) + red[tid][2]) + red[tid][3];
+}
+
+// The same in the geometry of k_psi_wide_f32; every wave keeps FP64 sums of
+// its own runs.
+template <int R>
+__global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))) void k_psi_wide_f64(
+    const ColDesc* __restrict__ cols, const Unit* __restrict__ units, int u0, int conditional) {
+  const Unit u = units[u0 + blockIdx.x];
+  const ColDesc c = cols[u.col];
+  if (!c.st->active) return;
+  if (conditional && !c.st->need_f64) return;
+  const double* x = c.x64;
+  const int n = c.n;
+  __shared__ double tile[2][kPsiTile];
+  __shared__ double red[2][kPsiWaves];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i0 = u.row * 64;
+  const int i = i0 + lane;
+  const double xi = (i < n) ? x[i] : 0.0;
+  const double ig2 = c.st->cd[0], cg = c.st->cd[1];
+  const int j_begin = max(u.j_begin, i0), j_end = unit_end(u, n);
+  double s = 0.0, a = 0.0;
+  if (j_begin + tid < j_end) tile[0][tid] = x[j_begin + tid];
+  __syncthreads();
+  for (int t0 = j_begin, b = 0; t0 < j_end; t0 += kPsiTile, b ^= 1) {
+    const int jn = t0 + kPsiTile + tid;
+    double next = 0.0;
+    if (jn < j_end) next = x[jn];
+    const int js = t0 + wave * kRun;
+    if (js < j_end) {
+      if (js == i0)
+        psi_run64<R, true>(&tile[b][wave * kRun], js, xi, i, ig2, cg, s, a);
+      else
+        psi_run64<R, false>(&tile[b][wave * kRun], js, xi, i, ig2, cg, s, a);
+    }
+    tile[b ^ 1][tid] = next;
+    __syncthreads();
+  }
+  const double v = wave_sum2((i < n) ? s : 0.0, (i < n) ? a : 0.0);
+  if ((lane & 31) == 0) red[lane >> 5][wave] = v;
+  __syncthreads();
+  if (tid < 2) {
+    double sum = red[tid][0];
+    for (int w = 1; w < kPsiWaves; ++w) sum += red[tid][w];
+    c.psi_part[(int64_t)tid * c.n_items_psi + u.item] = sum;
+  }
 }
 
 // ------------------------------------------------------------------ LSCV kernels
@@ -647,8 +772,8 @@ __device__ __forceinline__ void lscv_run(const float4* __restrict__ tile, int jl
 // One LSCV work unit of the vector-ALU sweep: the unit's row of 256 samples
 // i against its j-range, for the HC bandwidths of its chunk; the block's
 // FP64 partial sums go to the unit's own slots.  TJ: samples per LDS tile
-// (256, 512 or 1024; a unit's j-range is a multiple of 512, so a 1024 tile
-// may end half full).  The tile size changes only how often the block stages
+// (256, 512 or 1024; a unit's j-range is a multiple of kRun, so a tile may
+// end partly full).  The tile size changes only how often the block stages
 // and synchronises: every lane still folds its terms in runs of 64 j in
 // ascending j order, so every (unit, h) sum is bitwise the same for all TJ.
 template <int HC, int TJ>
@@ -672,8 +797,9 @@ __device__ __forceinline__ void lscv_unit_f32(const ColDesc* __restrict__ cols, 
     ck[k] = uniform_f32(cc[k]);
     a1[k] = a2[k] = 0.0;
   }
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += TJ) {
-    const int te = min(t0 + TJ, u.j_end);
+  const int j_end = unit_end(u, n);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += TJ) {
+    const int te = min(t0 + TJ, j_end);
     __syncthreads();
     for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
     __syncthreads();
@@ -687,15 +813,13 @@ __device__ __forceinline__ void lscv_unit_f32(const ColDesc* __restrict__ cols, 
     }
   }
   const bool valid = i < n;
+  double v[2 * HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    const double v1 = wave_sum(valid ? a1[k] : 0.0);
-    const double v2 = wave_sum(valid ? a2[k] : 0.0);
-    if (lane == 0) {
-      red[wave][2 * k] = v1;
-      red[wave][2 * k + 1] = v2;
-    }
+    v[2 * k] = valid ? a1[k] : 0.0;
+    v[2 * k + 1] = valid ? a2[k] : 0.0;
   }
+  wave_sums(v, red[wave], lane);
   __syncthreads();
   if (tid < 2 * HC) {
     const int h = u.chunk * HC + (tid >> 1);
@@ -800,11 +924,11 @@ void k_lscv_units_prune(const ColDesc* __restrict__ cols, const Unit* __restrict
   const float* x = c.x32;
   const int n = c.n;
   const int row0 = u.row * kBI;
-  int j_end = u.j_end;
+  int j_end = unit_end(u, n);
   {
     const float row_max = x[min(row0 + kBI, n) - 1];
     const float cut = c.d2cut[u.chunk];
-    for (int t = u.j_begin; t < u.j_end; t += kBJ) {
+    for (int t = u.j_begin; t < j_end; t += kBJ) {
       const float dd = x[t] - row_max;
       if (dd > 0.f && dd * dd > cut) {
         j_end = t;
@@ -828,11 +952,11 @@ void k_lscv_units_prune(const ColDesc* __restrict__ cols, const Unit* __restrict
     a1[k] = a2[k] = 0.0;
   }
   for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
-    for (int q = tid; q < kBJ / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
+    for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
     __syncthreads();
     int js = max(t0, wave_i0);
-    const int te = t0 + kBJ;
     if (js < te) {
       if (js == wave_i0) {
         lscv_run<HC, true>(tile, js - t0, js, xi, i, ck, a1, a2);
@@ -848,15 +972,13 @@ void k_lscv_units_prune(const ColDesc* __restrict__ cols, const Unit* __restrict
     atomicAdd(&c.st->pruned_evals, rows * (double)(min(u.j_end, n) - j_end) * hv);
   }
   const bool valid = i < n;
+  double v[2 * HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    const double v1 = wave_sum(valid ? a1[k] : 0.0);
-    const double v2 = wave_sum(valid ? a2[k] : 0.0);
-    if (lane == 0) {
-      red[wave][2 * k] = v1;
-      red[wave][2 * k + 1] = v2;
-    }
+    v[2 * k] = valid ? a1[k] : 0.0;
+    v[2 * k + 1] = valid ? a2[k] : 0.0;
   }
+  wave_sums(v, red[wave], lane);
   __syncthreads();
   if (tid < 2 * HC) {
     const int h = u.chunk * HC + (tid >> 1);
@@ -942,13 +1064,14 @@ __global__ __launch_bounds__(kThreads) void k_lscv_units_f64(const ColDesc* __re
     ck[k] = cc[k];
     s1[k] = s2[k] = 0.0;
   }
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+  const int j_end = unit_end(u, n);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
-    for (int q = tid; q < kBJ / 2; q += kThreads)
+    for (int q = tid; q < (te - t0) / 2; q += kThreads)
       reinterpret_cast<double2*>(tile)[q] = reinterpret_cast<const double2*>(x + t0)[q];
     __syncthreads();
     int js = max(t0, wave_i0);
-    const int te = t0 + kBJ;
     if (js < te) {
       if (js == wave_i0) {
         lscv_run64<HC, true>(tile, js - t0, js, xi, i, ck, s1, s2);
@@ -958,15 +1081,13 @@ __global__ __launch_bounds__(kThreads) void k_lscv_units_f64(const ColDesc* __re
     }
   }
   const bool valid = i < n;
+  double v[2 * HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    const double v1 = wave_sum(valid ? s1[k] : 0.0);
-    const double v2 = wave_sum(valid ? s2[k] : 0.0);
-    if (lane == 0) {
-      red[wave][2 * k] = v1;
-      red[wave][2 * k + 1] = v2;
-    }
+    v[2 * k] = valid ? s1[k] : 0.0;
+    v[2 * k + 1] = valid ? s2[k] : 0.0;
   }
+  wave_sums(v, red[wave], lane);
   __syncthreads();
   if (tid < 2 * HC) {
     const int h = u.chunk * HC + (tid >> 1);
@@ -1069,11 +1190,12 @@ __global__ __launch_bounds__(kThreads) void k_lscv_units_mfma(const ColDesc* __r
   const float bop = (kb == (colb >> 4)) ? c.c32[u.chunk * HC + (colb & 15)] : 0.f;
   float a1 = 0.f, c1 = 0.f, a2 = 0.f, c2 = 0.f;
   const bool rows_full = wave_i0 + 64 <= n;
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+  const int j_end = unit_end(u, n);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
-    for (int q = tid; q < kBJ / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
+    for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
     __syncthreads();
-    const int te = t0 + kBJ;
     for (int js = max(t0, wave_i0); js < te; js += 16) {
       float s1[4] = {0.f, 0.f, 0.f, 0.f}, s2[4] = {0.f, 0.f, 0.f, 0.f};
       const bool clean = rows_full && js >= wave_i0 + 64 && js + 16 <= n;
@@ -1234,22 +1356,26 @@ void launch_lscv_finalize(hipStream_t s, const ColDesc* cols, const int* ids, in
   if (n_ids > 0) k_lscv_finalize<<<n_ids, 1024, 0, s>>>(cols, ids, f64);
 }
 
-void launch_psi_units(hipStream_t s, int r, int f64, int conditional, const ColDesc* cols, const Unit* units, int u0,
-                      int n_units) {
+void launch_psi_units(hipStream_t s, int r, int f64, int conditional, int wide, const ColDesc* cols,
+                      const Unit* units, int u0, int n_units) {
   if (n_units <= 0) return;
-  if (f64) {
-    switch (r) {
-      case 8: k_psi_units_f64<8><<<n_units, kThreads, 0, s>>>(cols, units, u0, conditional); break;
-      case 6: k_psi_units_f64<6><<<n_units, kThreads, 0, s>>>(cols, units, u0, conditional); break;
-      default: k_psi_units_f64<4><<<n_units, kThreads, 0, s>>>(cols, units, u0, conditional); break;
-    }
-  } else {
-    switch (r) {
-      case 8: k_psi_units_f32<8><<<n_units, kThreads, 0, s>>>(cols, units, u0); break;
-      case 6: k_psi_units_f32<6><<<n_units, kThreads, 0, s>>>(cols, units, u0); break;
-      default: k_psi_units_f32<4><<<n_units, kThreads, 0, s>>>(cols, units, u0); break;
-    }
+  const int t = wide ? kPsiThreads : kThreads;
+#define KDE_PSI_CASE(RR)                                                                            \
+  if (f64 && wide)                                                                                  \
+    k_psi_wide_f64<RR><<<n_units, t, 0, s>>>(cols, units, u0, conditional);                         \
+  else if (f64)                                                                                     \
+    k_psi_units_f64<RR><<<n_units, t, 0, s>>>(cols, units, u0, conditional);                        \
+  else if (wide)                                                                                    \
+    k_psi_wide_f32<RR><<<n_units, t, 0, s>>>(cols, units, u0);                                      \
+  else                                                                                              \
+    k_psi_units_f32<RR><<<n_units, t, 0, s>>>(cols, units, u0);                                     \
+  break
+  switch (r) {
+    case 8: KDE_PSI_CASE(8);
+    case 6: KDE_PSI_CASE(6);
+    default: KDE_PSI_CASE(4);
   }
+#undef KDE_PSI_CASE
 }
 
 void launch_zero_ints(hipStream_t s, int* p, int n) {

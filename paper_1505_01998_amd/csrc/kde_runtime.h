@@ -50,6 +50,8 @@ struct ColPlan {
   double grid_lo = 0.0, grid_hi = 0.0;
   std::vector<double> grid_h;  // explicit grid
   ColItems psi_items, lscv_items;
+  int psi_groups = 1;   // psi units (and partial-sum slots) per work item: 1, or kPsiGroups of 64 samples i
+  int lscv_pieces = 1;  // LSCV units (and partial-sum slots) per work item and bandwidth chunk
   // tile pruning (mixed form, LSCV): a sorted copy of the column, the first
   // j-tile of every row as "near" items, and per-chunk cut distances
   bool prune = false;
@@ -87,6 +89,14 @@ struct IterPlan {
   std::vector<Unit> psi_units[3];
   std::vector<UnitCost> psi_cost[3];
   std::vector<RowDesc> psi_rows[3];
+  // Columns added whole (add_full_column) run the same units in every stage
+  // and in its FP64 re-run: one list, psi_units[1], serves them all.  A column
+  // of two stages takes no part in stage 0; once one is added stage 0 has a
+  // list of its own.
+  bool psi_shared = false, psi_two_stage = false;
+  // units [0, psi_narrow) of a list have rows of 256 samples i, the rest of 64
+  int psi_narrow[3] = {0, 0, 0}, psi_cond_narrow[3] = {0, 0, 0};
+  int psi_list(int stage) const { return !psi_shared || (stage == 0 && psi_two_stage) ? stage : 1; }
   std::vector<Unit> psi_cond_units[3];  // FP64 re-run (mixed form), of columns finishing the stage
   std::vector<UnitCost> psi_cond_cost[3];
   std::vector<int> ids_plugin_final;
@@ -270,12 +280,31 @@ std::string check_request(const kde_request& r);
 constexpr int kSegRefHC = 16;
 // Work items of a column of n samples for items of `seg` samples (0: whole rows).
 void make_items(int64_t n, int64_t seg, ColItems& out);
+// A column of fewer psi items than this runs them as units of 64 samples i:
+// the blocks of 256 would fill less than four rounds of the 2048 that the
+// chip holds (n < 3.4e5 at the default launch size).
+constexpr size_t kPsiWideItems = 8192;
 // Item length of a pass whose blocks evaluate `hc` terms per pair.
 int64_t pick_seg(const kde_ctx* c, int64_t n, int hc);
 // Units a pass may hold before the planner lengthens its items.
 constexpr double kMaxUnits = 16777216.0;
 // pick_seg, lengthened while items x chunks would exceed kMaxUnits.
 int64_t capped_seg(const kde_ctx* c, int64_t n, int hc, double chunks);
+// How a pass over one column is cut: item length (0: whole rows) and the
+// pieces each item is cut into along j.
+struct Split {
+  int64_t seg;
+  int pieces;
+};
+// capped_seg, shortened (and the shortest items cut into pieces) until the
+// pass holds about `fill` units, `chunks` of them an item and piece.
+Split pick_split(const kde_ctx* c, int64_t n, double chunks, double fill);
+// Units that fill the chip with a few rounds of resident blocks.  Fewer leave a longer last round, more spend more on
+// each unit's start and end and on the planner: LSCV at 2048 / 3072 / 4096 /
+// 8192 units, n = 4e4 x 128: 11.3 / 11.0 / 10.7 / 11.0 ms a call, n = 5000 x
+// 128: 0.446 / 0.447 / 0.494 / 0.65 ms, 48 columns of n = 1e3 to 3e4: 45.4 /
+// 45.9 / 46.9 ms (the first three).
+constexpr double kFillLscv = 3072.0;
 // Sets c->job_hc / job_mfma for a synchronous job over these requests: the
 // options, or with the autotune option the tuned vector-ALU variant of the
 // job's largest LSCV column (tuning that shape first when the job is large).
@@ -289,7 +318,9 @@ kde_status stage_column(kde_ctx* c, kde_column x, const ColDesc** dcol);
 // returns the cached decision for that shape).
 kde_status tune_shape(kde_ctx* c, int64_t n, int n_h, TuneChoice& out);
 // Fills the work decomposition and block layout of one request's column.
-std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p);
+// fill: cut LSCV passes that hold too few units further (pick_split); false
+// gives the cut by launch size alone, which older checkpoints use.
+std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p, bool fill = true);
 // Points a descriptor at a column block; raw is the caller's device column
 // (ignored when the plan keeps the samples in the block); st is its state.
 void bind_column(const ColPlan& p, char* block, const void* raw, DevState* st, ColDesc& d);

@@ -90,6 +90,7 @@ void IterPlan::clear() {
   prune_units.clear();
   prune_cost.clear();
   max_stat_blocks = 1;
+  psi_shared = psi_two_stage = false;
 }
 
 // ---- argument checks
@@ -118,12 +119,15 @@ std::string check_grid(const kde_grid& g) {
 }
 
 // ---- work items
-// Pairs i < j with i in the row's 256 samples, j in [jb, je), both < n:
+double row_pairs(int64_t n, int64_t i0, int64_t rows, int64_t jb, int64_t je);
+
+// Pairs i < j with i in the row's samples, j in [jb, je), both < n:
 // sum over i of max(0, je - max(jb, i + 1)) in closed form (rows i < jb
 // contribute je - jb each, rows i >= jb the arithmetic series je - 1 - i).
-double item_pairs(int64_t n, int64_t row, int64_t jb, int64_t je) {
-  const int64_t i0 = row * kBI;
-  const int64_t i1 = std::min<int64_t>(n, i0 + kBI);
+double item_pairs(int64_t n, int64_t row, int64_t jb, int64_t je) { return row_pairs(n, row * kBI, kBI, jb, je); }
+
+double row_pairs(int64_t n, int64_t i0, int64_t rows, int64_t jb, int64_t je) {
+  const int64_t i1 = std::min<int64_t>(n, i0 + rows);
   je = std::min<int64_t>(je, n);
   int64_t p = 0;
   const int64_t flat_end = std::min(i1, jb);  // i in [i0, flat_end): j from jb
@@ -153,9 +157,14 @@ void make_items(int64_t n, int64_t seg, ColItems& out) {
       pr.push_back(p);
     }
   }
-  std::vector<size_t> order(pr.size());
-  for (size_t k = 0; k < order.size(); ++k) order[k] = k;
-  std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return pr[a] > pr[b]; });
+  // longest first: the full items as they come, then the others sorted
+  double most = 0.0;
+  for (double p : pr) most = std::max(most, p);
+  std::vector<size_t> order, rest;
+  order.reserve(pr.size());
+  for (size_t k = 0; k < pr.size(); ++k) (pr[k] == most ? order : rest).push_back(k);
+  std::stable_sort(rest.begin(), rest.end(), [&](size_t a, size_t b) { return pr[a] > pr[b]; });
+  order.insert(order.end(), rest.begin(), rest.end());
   out.row.resize(order.size());
   out.jb.resize(order.size());
   out.je.resize(order.size());
@@ -197,6 +206,30 @@ int64_t capped_seg(const kde_ctx* c, int64_t n, int hc, double chunks) {
   return seg >= n ? 0 : seg;
 }
 
+// A pass of few units leaves the chip idle: a lone wave on a SIMD runs the
+// sweeps at about half the rate of four, and a column of n = 1000 x 100
+// bandwidths has 28 units of whole rows for 256 CUs.  Items are therefore
+// shortened to the tile while the pass holds fewer than `fill` units, and
+// tile-long items cut into 2, 4 or 8 pieces of at least 64 samples (one plain
+// FP32 run, so the runs and their sums stay as they are; only the FP64 sums
+// over them are grouped anew).  The cut depends on n and the grid size alone.
+// A call with three plug-in stages: n = 5000 x 128 bandwidths 1.87 -> 0.45
+// ms, n = 12345 x 150 5.4 -> 1.6 ms, n = 4e4 x 128 17.9 -> 11.0 ms.
+Split pick_split(const kde_ctx* c, int64_t n, double chunks, double fill) {
+  Split s{capped_seg(c, n, kSegRefHC, chunks), 1};
+  if (c->opt_seg >= 0) return s;
+  const int64_t rows = (n + kBI - 1) / kBI;
+  const double row_samples = 0.5 * (double)n * (double)n / kBI + 0.5 * (double)n;
+  int64_t seg = (int64_t)(row_samples * chunks / fill);
+  seg = std::max<int64_t>(kBJ, seg / kBJ * kBJ);
+  if (s.seg == 0 || s.seg > seg) s.seg = seg >= n ? 0 : seg;
+  if (seg > kBJ) return s;
+  double items = 0.0;  // of at most kBJ samples
+  for (int64_t r = 0; r < rows; ++r) items += (double)((n - r * kBI + kBJ - 1) / kBJ);
+  while (s.pieces < kBJ / 64 && items * s.pieces * 2 * chunks <= fill) s.pieces *= 2;
+  return s;
+}
+
 namespace {
 
 size_t take(size_t& at, size_t bytes) {
@@ -214,7 +247,7 @@ std::string check_request(const kde_request& r) {
   return e;
 }
 
-std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p) {
+std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p, bool fill) {
   std::string e = check_request(r);
   p = ColPlan();
   p.plugin = (r.methods & KDE_METHOD_PLUGIN) != 0;
@@ -225,10 +258,12 @@ std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p) {
   p.f64 = r.x.dtype == KDE_F64;
   p.stages = p.plugin ? r.stages : 0;
   p.hc = all64 ? 8 : c->job_hc;
-  // psi items are cut like one LSCV chunk's (about 7.6e6 pairs a block at
-  // the default launch size): a stage's pass then spans ~30 rounds of the
-  // blocks the chip holds, so its partly filled last round costs little
-  if (p.plugin) make_items(p.n, capped_seg(c, p.n, kSegRefHC, 1.0), p.psi_items);
+  // psi items are cut by the launch size alone: the compensated sums of a
+  // stage depend on where the items begin and end
+  if (p.plugin) {
+    make_items(p.n, capped_seg(c, p.n, kSegRefHC, 1.0), p.psi_items);
+    p.psi_groups = p.psi_items.pairs.size() < kPsiWideItems ? kPsiGroups : 1;
+  }
   if (p.lscv) {
     p.n_h = r.grid.n_h;
     p.n_chunks = (p.n_h + p.hc - 1) / p.hc;
@@ -236,8 +271,11 @@ std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p) {
     p.grid_lo = r.grid.lo;
     p.grid_hi = r.grid.hi;
     if (r.grid.kind == KDE_GRID_EXPLICIT) p.grid_h.assign(r.grid.h, r.grid.h + p.n_h);
-    make_items(p.n, capped_seg(c, p.n, kSegRefHC, (double)((p.n_h + kSegRefHC - 1) / kSegRefHC)), p.lscv_items);
     p.prune = c->opt_prune && !all64;
+    const double chunks = (double)((p.n_h + kSegRefHC - 1) / kSegRefHC);
+    const Split s = fill ? pick_split(c, p.n, chunks, kFillLscv) : Split{capped_seg(c, p.n, kSegRefHC, chunks), 1};
+    if (!p.prune) p.lscv_pieces = s.pieces;
+    make_items(p.n, s.seg, p.lscv_items);
     if (p.prune) {
       // the first j-tile of every row: j in [row0, row0 + kBJ)
       const int rows = (p.n + kBI - 1) / kBI;
@@ -262,7 +300,7 @@ std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p) {
   p.off_nf = take(at, 4 * kStatBlocks);
   if (p.plugin) {
     if (!all64) p.off_y32 = take(at, 4 * xn);
-    p.off_psi_part = take(at, 16 * p.psi_items.pairs.size());
+    p.off_psi_part = take(at, 16 * p.psi_items.pairs.size() * p.psi_groups);
     p.off_psi_sums = take(at, 16);
   }
   if (p.lscv) {
@@ -271,7 +309,7 @@ std::string plan_column(const kde_ctx* c, const kde_request& r, ColPlan& p) {
     p.off_h = take(at, 8 * m);
     p.off_c32 = take(at, 4 * m);
     p.off_c64 = take(at, 8 * m);
-    p.off_part = take(at, 16 * (size_t)p.n_h * p.lscv_items.pairs.size());
+    p.off_part = take(at, 16 * (size_t)p.n_h * p.lscv_items.pairs.size() * p.lscv_pieces);
     p.off_sums = take(at, 16 * (size_t)p.n_h);
     p.off_g = take(at, 8 * (size_t)p.n_h);
     p.off_gs = take(at, 8 * (size_t)p.n_h);
@@ -318,8 +356,8 @@ void bind_column(const ColPlan& p, char* b, const void* raw, DevState* st, ColDe
   d.raw_f64 = p.f64;
   d.n_h = p.lscv ? p.n_h : 0;
   d.n_chunks = p.n_chunks;
-  d.n_items = (int)p.lscv_items.pairs.size();
-  d.n_items_psi = (int)p.psi_items.pairs.size();
+  d.n_items = (int)p.lscv_items.pairs.size() * p.lscv_pieces;
+  d.n_items_psi = (int)p.psi_items.pairs.size() * p.psi_groups;
   d.grid_kind = p.grid_kind;
   d.grid_lo = p.grid_lo;
   d.grid_hi = p.grid_hi;
@@ -338,29 +376,50 @@ void init_state(const ColPlan& p, double fp64_kappa, DevState& h) {
   h.fp64_kappa = fp64_kappa;
 }
 
+namespace {
+
+// Piece q of `pieces` of item `it`: its j-range and the pairs in it.  A piece
+// may hold no pair (padding); its unit still runs, since it writes its slot.
+double piece_of(const ColItems& items, size_t it, int n, int pieces, int q, int& jb, int& je) {
+  const int len = (items.je[it] - items.jb[it]) / pieces;
+  jb = items.jb[it] + q * len;
+  je = jb + len;
+  return pieces == 1 ? items.pairs[it] : item_pairs(n, items.row[it], jb, je);
+}
+
+}  // namespace
+
 void psi_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost) {
-  for (size_t it = 0; it < p.psi_items.pairs.size(); ++it) {
-    u.push_back(Unit{id, p.psi_items.row[it], p.psi_items.jb[it], p.psi_items.je[it], (int)it, 0});
-    cost.push_back(UnitCost{p.psi_items.pairs[it], p.psi_items.pairs[it]});
-  }
+  const int G = p.psi_groups, rows = kBI / G;
+  for (size_t it = 0; it < p.psi_items.pairs.size(); ++it)
+    for (int q = 0; q < G; ++q) {
+      const int row = p.psi_items.row[it] * G + q, jb = p.psi_items.jb[it], je = p.psi_items.je[it];
+      const double pairs = row_pairs(p.n, (int64_t)row * rows, rows, jb, je);
+      u.push_back(Unit{id, row, jb, je, (int)it * G + q, G > 1 ? 1 : 0});
+      cost.push_back(UnitCost{pairs, pairs});
+    }
 }
 
 void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost) {
+  const int P = p.lscv_pieces;
   for (size_t it = 0; it < p.lscv_items.pairs.size(); ++it)
-    for (int ch = 0; ch < p.n_chunks; ++ch) {
-      u.push_back(Unit{id, p.lscv_items.row[it], p.lscv_items.jb[it], p.lscv_items.je[it], (int)it, ch});
-      const int valid = std::min(p.hc, p.n_h - ch * p.hc);
-      cost.push_back(UnitCost{p.lscv_items.pairs[it], p.lscv_items.pairs[it] * valid});
+    for (int q = 0; q < P; ++q) {
+      int jb, je;
+      const double pairs = piece_of(p.lscv_items, it, p.n, P, q, jb, je);
+      for (int ch = 0; ch < p.n_chunks; ++ch) {
+        u.push_back(Unit{id, p.lscv_items.row[it], jb, je, (int)it * P + q, ch});
+        cost.push_back(UnitCost{pairs, pairs * std::min(p.hc, p.n_h - ch * p.hc)});
+      }
     }
 }
 
 void psi_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows) {
-  const int m = (int)p.psi_items.pairs.size();
+  const int m = d.n_items_psi;
   for (int w = 0; w < 2; ++w) rows.push_back(RowDesc{d.psi_part + (size_t)w * m, d.psi_sums + w, m, 0});
 }
 
 void lscv_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows) {
-  const int m = (int)p.lscv_items.pairs.size();
+  const int m = d.n_items;
   for (int r = 0; r < 2 * p.n_h; ++r) rows.push_back(RowDesc{d.part + (size_t)r * m, d.sums + r, m, 0});
 }
 
@@ -399,15 +458,20 @@ void add_full_column(const kde_ctx* c, const ColPlan& p, const ColDesc& d, int i
   if (p.raw_in_block) it.uploads.push_back(Upload{(void*)d.raw, host_raw, p.raw_bytes});
   it.ids_stats.push_back(id);
   it.max_stat_blocks = std::max(it.max_stat_blocks, std::min(kStatBlocks, (p.n + 2047) / 2048));
-  const bool cond = c->prec != KDE_PREC_FP64 && c->opt_fp64_kappa > 0.0;
   if (p.plugin) {
     for (int s = (p.stages == 3 ? 0 : 1); s < 3; ++s) {
       it.ids_begin[s].push_back(id);
-      psi_units_of(p, id, it.psi_units[s], it.psi_cost[s]);
       psi_rows_of(p, d, it.psi_rows[s]);
       it.ids_finish[s].push_back(id);
-      if (cond) psi_units_of(p, id, it.psi_cond_units[s], it.psi_cond_cost[s]);
     }
+    it.psi_shared = true;
+    if (p.stages != 3 && !it.psi_two_stage) {
+      it.psi_two_stage = true;
+      it.psi_units[0] = it.psi_units[1];
+      it.psi_cost[0] = it.psi_cost[1];
+    }
+    if (p.stages == 3 && it.psi_two_stage) psi_units_of(p, id, it.psi_units[0], it.psi_cost[0]);
+    psi_units_of(p, id, it.psi_units[1], it.psi_cost[1]);
     it.ids_plugin_final.push_back(id);
   }
   if (p.lscv) {
@@ -463,17 +527,45 @@ kde_status collect_timing(kde_ctx* c) {
   return KDE_OK;
 }
 
-// Sorts units largest first (the order blocks are dispatched in); results do
-// not depend on it, since every unit writes its own partial-sum slot.
+// Puts units largest first (the order blocks are dispatched in); results do
+// not depend on it, since every unit writes its own partial-sum slot.  Units
+// of one column come in that order; several columns' are dealt into 1024
+// classes of size in one pass (a comparison sort of the 290,000 psi and
+// 150,000 LSCV units of 48 columns cost more than their psi kernels).
 // scatter: units of equal planned size are put in a fixed pseudo-random
 // order instead of (item, chunk) order.  With tile pruning their real cost
 // depends strongly on the chunk (small bandwidths skip most tiles), and
 // consecutive blocks are dealt round-robin to the chip's eight dies, so in
 // (item, chunk) order each die would always get the same chunks.
 void sort_units(std::vector<Unit>& u, std::vector<UnitCost>& cost, bool scatter = false) {
+  if (!scatter) {
+    constexpr int kClasses = 1024;
+    double most = 0.0;
+    bool sorted = true;
+    for (size_t k = 0; k < cost.size(); ++k) {
+      most = std::max(most, cost[k].pairs);
+      sorted = sorted && (k == 0 || cost[k - 1].pairs >= cost[k].pairs);
+    }
+    if (sorted) return;
+    const double scale = (kClasses - 1) / most;
+    std::vector<size_t> at(kClasses + 1, 0);
+    auto cls = [&](size_t k) { return kClasses - 1 - (int)(cost[k].pairs * scale); };
+    for (size_t k = 0; k < cost.size(); ++k) ++at[cls(k) + 1];
+    for (int q = 0; q < kClasses; ++q) at[q + 1] += at[q];
+    std::vector<Unit> u2(u.size());
+    std::vector<UnitCost> c2(u.size());
+    for (size_t k = 0; k < cost.size(); ++k) {
+      const size_t o = at[cls(k)]++;
+      u2[o] = u[k];
+      c2[o] = cost[k];
+    }
+    u.swap(u2);
+    cost.swap(c2);
+    return;
+  }
   std::vector<size_t> o(u.size());
   for (size_t k = 0; k < o.size(); ++k) o[k] = k;
-  std::vector<uint32_t> key(scatter ? u.size() : 0);
+  std::vector<uint32_t> key(u.size());
   for (size_t k = 0; k < key.size(); ++k) {
     uint32_t h = (uint32_t)u[k].item * 0x9E3779B1u ^ (uint32_t)u[k].chunk * 0x85EBCA77u ^ (uint32_t)u[k].col;
     h ^= h >> 15;
@@ -483,7 +575,7 @@ void sort_units(std::vector<Unit>& u, std::vector<UnitCost>& cost, bool scatter 
   }
   std::stable_sort(o.begin(), o.end(), [&](size_t a, size_t b) {
     if (cost[a].pairs != cost[b].pairs) return cost[a].pairs > cost[b].pairs;
-    return scatter && key[a] < key[b];
+    return key[a] < key[b];
   });
   std::vector<Unit> u2(u.size());
   std::vector<UnitCost> c2(u.size());
@@ -493,6 +585,26 @@ void sort_units(std::vector<Unit>& u, std::vector<UnitCost>& cost, bool scatter 
   }
   u.swap(u2);
   cost.swap(c2);
+}
+
+// Puts the psi units of 256 samples i first, each kind largest first; the
+// count of that kind.
+int sort_psi_units(std::vector<Unit>& u, std::vector<UnitCost>& cost) {
+  size_t narrow = 0;
+  for (const Unit& x : u) narrow += x.chunk == 0;
+  sort_units(u, cost);
+  if (narrow == 0 || narrow == u.size()) return (int)narrow;
+  std::vector<Unit> u2(u.size());
+  std::vector<UnitCost> c2(u.size());
+  size_t at[2] = {0, narrow};
+  for (size_t k = 0; k < u.size(); ++k) {
+    const size_t o = at[u[k].chunk]++;
+    u2[o] = u[k];
+    c2[o] = cost[k];
+  }
+  u.swap(u2);
+  cost.swap(c2);
+  return (int)narrow;
 }
 
 // Groups of the persistent dense sweep: the largest-first list is split,
@@ -545,11 +657,13 @@ void group_units(std::vector<Unit>& u, std::vector<UnitCost>& cost, const std::v
 // Launch ranges over units [0, n) whose summed evaluations stay within
 // budget, with at least 2048 blocks per launch when the list has them, so a
 // launch fills the chip.  FP64 terms cost about five times the FP32 ones.
+// first, last: the units of the list to launch (last < 0: to its end).
 template <typename F>
-kde_status for_each_launch(const kde_ctx* c, const std::vector<UnitCost>& cost, bool f64, F&& launch) {
+kde_status for_each_launch(const kde_ctx* c, const std::vector<UnitCost>& cost, bool f64, F&& launch, int first = 0,
+                           int last = -1) {
   const double budget = f64 ? c->opt_launch_evals / 5.0 : c->opt_launch_evals;
-  size_t u0 = 0;
-  const size_t end = cost.size();
+  size_t u0 = (size_t)first;
+  const size_t end = last < 0 ? cost.size() : (size_t)last;
   while (u0 < end) {
     double acc = cost[u0].evals;
     size_t u1 = u0 + 1;
@@ -627,8 +741,8 @@ kde_status sync_and_check(kde_ctx* c) {
 kde_status pack_pass(kde_ctx* c, IterPlan& it, PassLayout& L) {
   kde_status s;
   for (int q = 0; q < 3; ++q) {
-    sort_units(it.psi_units[q], it.psi_cost[q]);
-    sort_units(it.psi_cond_units[q], it.psi_cond_cost[q]);
+    it.psi_narrow[q] = sort_psi_units(it.psi_units[q], it.psi_cost[q]);
+    it.psi_cond_narrow[q] = sort_psi_units(it.psi_cond_units[q], it.psi_cond_cost[q]);
   }
   sort_units(it.lscv_units, it.lscv_cost);
   if (lscv_queue_form(c, it)) {
@@ -646,10 +760,12 @@ kde_status pack_pass(kde_ctx* c, IterPlan& it, PassLayout& L) {
   for (int q = 0; q < 3; ++q) {
     L.o_begin[q] = b.add(it.ids_begin[q].data(), vbytes(it.ids_begin[q]));
     L.o_finish[q] = b.add(it.ids_finish[q].data(), vbytes(it.ids_finish[q]));
-    L.o_psu[q] = b.add(it.psi_units[q].data(), vbytes(it.psi_units[q]));
+    if (it.psi_list(q) == q) L.o_psu[q] = b.add(it.psi_units[q].data(), vbytes(it.psi_units[q]));
     L.o_pr[q] = b.add(it.psi_rows[q].data(), vbytes(it.psi_rows[q]));
-    L.o_pc[q] = b.add(it.psi_cond_units[q].data(), vbytes(it.psi_cond_units[q]));
+    if (!it.psi_shared) L.o_pc[q] = b.add(it.psi_cond_units[q].data(), vbytes(it.psi_cond_units[q]));
   }
+  if (it.psi_shared)
+    for (int q = 0; q < 3; ++q) L.o_pc[q] = L.o_psu[q] = L.o_psu[it.psi_list(q)];
   L.o_pf = b.add(it.ids_plugin_final.data(), vbytes(it.ids_plugin_final));
   L.o_lp = b.add(it.ids_lscv_prep.data(), vbytes(it.ids_lscv_prep));
   L.o_lu = b.add(it.lscv_units.data(), vbytes(it.lscv_units));
@@ -704,25 +820,40 @@ kde_status launch_pass(kde_ctx* c, const IterPlan& it, const PassLayout& L) {
     const int r = 8 - 2 * q;
     kde::launch_psi_begin(st, cols, ids(L.o_begin[q]), (int)it.ids_begin[q].size(), q, all64 ? 1 : 0);
     const Unit* pu = (const Unit*)(d + L.o_psu[q]);
-    s = for_each_launch(c, it.psi_cost[q], all64, [&](int u0, int cnt, double evals) -> kde_status {
-      kde_ctx::Pending pd{nullptr, nullptr, kde::kFamPsi, evals};
-      kde_status s2 = timed_begin(c, pd);
-      if (s2) return s2;
-      kde::launch_psi_units(st, r, all64 ? 1 : 0, 0, cols, pu, u0, cnt);
-      return timed_end(c, pd);
-    });
-    if (s) return s;
+    const std::vector<UnitCost>& cost = it.psi_cost[it.psi_list(q)];
+    const int narrow = it.psi_narrow[it.psi_list(q)];
+    for (int wide = 0; wide < 2; ++wide) {
+      s = for_each_launch(
+          c, cost, all64,
+          [&](int u0, int cnt, double evals) -> kde_status {
+            kde_ctx::Pending pd{nullptr, nullptr, kde::kFamPsi, evals};
+            kde_status s2 = timed_begin(c, pd);
+            if (s2) return s2;
+            kde::launch_psi_units(st, r, all64 ? 1 : 0, 0, wide, cols, pu, u0, cnt);
+            return timed_end(c, pd);
+          },
+          wide ? narrow : 0, wide ? -1 : narrow);
+      if (s) return s;
+    }
     kde::launch_reduce_rows(st, (const RowDesc*)(d + L.o_pr[q]), (int)it.psi_rows[q].size());
     kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, all64 ? 1 : 0, 0);
-    if (!all64 && !it.psi_cond_units[q].empty()) {
+    const std::vector<UnitCost>& cond_cost = it.psi_shared ? it.psi_cost[it.psi_list(q)] : it.psi_cond_cost[q];
+    const bool cond = it.psi_shared ? c->opt_fp64_kappa > 0.0 : !cond_cost.empty();
+    if (!all64 && cond && !cond_cost.empty()) {
       // FP64 re-run of the columns whose stage is badly conditioned; blocks of
       // other columns exit at once, so these launches are not timed.
       const Unit* pc = (const Unit*)(d + L.o_pc[q]);
-      s = for_each_launch(c, it.psi_cond_cost[q], true, [&](int u0, int cnt, double) -> kde_status {
-        kde::launch_psi_units(st, r, 1, 1, cols, pc, u0, cnt);
-        return KDE_OK;
-      });
-      if (s) return s;
+      const int cond_narrow = it.psi_shared ? narrow : it.psi_cond_narrow[q];
+      for (int wide = 0; wide < 2; ++wide) {
+        s = for_each_launch(
+            c, cond_cost, true,
+            [&](int u0, int cnt, double) -> kde_status {
+              kde::launch_psi_units(st, r, 1, 1, wide, cols, pc, u0, cnt);
+              return KDE_OK;
+            },
+            wide ? cond_narrow : 0, wide ? -1 : cond_narrow);
+        if (s) return s;
+      }
       kde::launch_reduce_rows(st, (const RowDesc*)(d + L.o_pr[q]), (int)it.psi_rows[q].size());
       kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, 1, 1);
     }
@@ -1281,8 +1412,8 @@ kde_status kde_plan_items(int64_t n, int32_t n_h, int64_t seg, int32_t cap, int3
   o.opt_seg = seg < 0 ? -1 : seg;
   kde::ColItems it;
   if (n_h > 0)
-    kde::make_items(n, kde::capped_seg(&o, n, kde::kSegRefHC, (double)((n_h + kde::kSegRefHC - 1) / kde::kSegRefHC)),
-                    it);
+    kde::make_items(
+        n, kde::pick_split(&o, n, (double)((n_h + kde::kSegRefHC - 1) / kde::kSegRefHC), kde::kFillLscv).seg, it);
   else
     kde::make_items(n, kde::capped_seg(&o, n, kde::kSegRefHC, 1.0), it);
   const int32_t m = (int32_t)it.pairs.size();
@@ -1396,7 +1527,8 @@ kde_status kde_lscv_item_sums(kde_ctx* c, kde_column x, const double* h_grid, in
   if ((s = run_single(c, make_req(x, KDE_METHOD_LSCV, 2, h_grid, n_h)))) return s;
   const kde::ColPlan& p = c->plans[0];
   const ColDesc& d = c->iter.cols[0];
-  const int32_t n_items = d.n_items;
+  const int32_t n_items = (int32_t)p.lscv_items.pairs.size();
+  const int P = p.lscv_pieces;
   std::vector<int32_t> idx((size_t)n_sel);
   for (int32_t k = 0; k < n_sel; ++k) {
     idx[k] = sel[k] < 0 ? n_items + sel[k] : sel[k];
@@ -1405,12 +1537,12 @@ kde_status kde_lscv_item_sums(kde_ctx* c, kde_column x, const double* h_grid, in
       return fail(c, KDE_E_INVAL, "item index out of range");
     }
   }
-  if ((s = ensure_out(c, (size_t)2 * n_h * (n_sel > 0 ? n_sel : 1)))) return s;
-  // the column's partials are laid out [2*n_h][n_items]: one strided column per selected item
+  if ((s = ensure_out(c, (size_t)2 * n_h * P * (n_sel > 0 ? n_sel : 1)))) return s;
+  // the column's partials are laid out [2*n_h][n_items][P]: one strided column per selected item
   for (int32_t k = 0; k < n_sel; ++k)
-    KDE_HIP_TRY(c, hipMemcpy2DAsync(c->h_out + (size_t)k * 2 * n_h, sizeof(double), d.part + idx[k],
-                                    sizeof(double) * (size_t)n_items, sizeof(double), (size_t)2 * n_h,
-                                    hipMemcpyDeviceToHost, c->stream));
+    KDE_HIP_TRY(c, hipMemcpy2DAsync(c->h_out + (size_t)k * 2 * n_h * P, sizeof(double) * P,
+                                    d.part + (size_t)idx[k] * P, sizeof(double) * (size_t)d.n_items,
+                                    sizeof(double) * P, (size_t)2 * n_h, hipMemcpyDeviceToHost, c->stream));
   if ((s = kde::sync_and_check(c))) return s;
   if ((s = map_status(c, c->h_st[0].status))) return s;
   *n_items_out = n_items;
@@ -1418,7 +1550,12 @@ kde_status kde_lscv_item_sums(kde_ctx* c, kde_column x, const double* h_grid, in
     ranges_out[3 * k] = p.lscv_items.row[idx[k]] * kde::kBI;
     ranges_out[3 * k + 1] = p.lscv_items.jb[idx[k]];
     ranges_out[3 * k + 2] = p.lscv_items.je[idx[k]];
-    std::memcpy(sums_out + (size_t)k * 2 * n_h, c->h_out + (size_t)k * 2 * n_h, sizeof(double) * 2 * n_h);
+    for (size_t r = 0; r < (size_t)2 * n_h; ++r) {
+      const double* v = c->h_out + ((size_t)k * 2 * n_h + r) * P;
+      double sum = v[0];
+      for (int q = 1; q < P; ++q) sum += v[q];
+      sums_out[(size_t)k * 2 * n_h + r] = sum;
+    }
   }
   return KDE_OK;
 }

@@ -1,0 +1,107 @@
+"""The cut of small passes: items of one tile cut into pieces of at least 64
+samples, each with its own partial-sum slot, and units that end at the last
+sample.  Checked where that can go wrong: columns around one run (64), one row
+(256) and one tile (512), and grids whose chunk count changes the number of
+pieces.  Bars as in test_gpu_parity.py: pair sums within 1e-5 (mixed, plus the
+FP32 range limit) and 1e-10 (FP64 form) of the oracle; the items' sums, each
+the sum of its pieces, add up to the pass's within 1e-12 (FP64 sums of at most
+a few thousand positive terms)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kde():
+    import paper_1505_01998_amd as kde
+
+    return kde
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("n,n_h", [(2, 1), (63, 5), (64, 16), (65, 17), (256, 100), (257, 1), (511, 33), (512, 128),
+                                   (513, 128), (1000, 100), (1025, 500), (3001, 40), (5003, 128)])
+def test_pieces_and_items_add_up(kde, precision, n, n_h):
+    x = workloads.draw("bimodal", n, 500 + n, np.float32)
+    grid = np.geomspace(0.02, 2.0, n_h) if n_h > 1 else np.array([0.3])
+    o = oracle.lscv_curve(x, grid)
+    tol = 1e-5 if precision == "mixed" else 1e-10
+    atol = n * (n - 1) / 2 * 2.0**-126
+    with kde.Context(0, precision) as c:
+        s1, s2 = c.lscv_sums(x, grid)
+        n_items, ranges, sums = c.lscv_item_sums(x, grid, np.arange(len(kde.kde_plan_items(n, n_h)[0])))
+        p = c.bw_plugin(x, 3)[1].psi if n > 64 else None
+    assert np.allclose(s1, o.s1, rtol=tol, atol=atol) and np.allclose(s2, o.s2, rtol=tol, atol=atol)
+    assert n_items == len(ranges)
+    assert np.allclose(sums[:, :, 0].sum(0), s1, rtol=1e-12, atol=0)
+    assert np.allclose(sums[:, :, 1].sum(0), s2, rtol=1e-12, atol=0)
+    for (i0, j0, j1), got in zip(ranges[:3], sums[:3]):
+        o1, _ = oracle.lscv_block_sums(x, int(i0), min(int(i0) + 256, n), int(j0), min(int(j1), n), grid)
+        assert np.allclose(got[:, 0], o1, rtol=tol, atol=atol)
+    if p is not None:
+        q = oracle.bw_plugin(x, 3)
+        for s in range(3):
+            assert p[s] == pytest.approx(q.psi[s], rel=1e-5 if precision == "mixed" else 1e-10 * max(1.0, q.kappa[s]))
+
+
+def _older(ck, n, n_h):
+    """The checkpoint as it was written with one psi slot an item: the header
+    names the items, the block lacks the other slots, and the cursor of an
+    interrupted stage counts items."""
+    def al(b):
+        return (b + 255) // 256 * 256
+
+    head = ck[:128].copy()
+    slots, _, block = head[64:88].view(np.int64)
+    items = slots // 4
+    gap = al(64 * items) - al(16 * items)
+    # samples, x32, x64, moment partials, their range and counts, y32
+    at = al(4 * n) + al(4 * (n + 768)) + al(8 * (n + 768)) + 8192 + 8192 + 4096 + al(4 * (n + 768))
+    start = ck.size - block - 16 * n_h  # the header's size
+    end = start + at + al(64 * items)
+    out = np.concatenate([ck[:start + at], ck[start + at:start + at + al(16 * items)], ck[end:]])
+    out[64:72].view(np.int64)[0] = items
+    out[80:88].view(np.int64)[0] = block - gap
+    cursor = out[112:120].view(np.int64)
+    cursor[0] = min(cursor[0] // 4, items)
+    return out
+
+
+@pytest.mark.parametrize("older", [False, True])
+@pytest.mark.parametrize("frac", [0.0, 0.02, 0.4, 1.0])
+def test_checkpoint_of_the_cut_by_launch_size_resumes(kde, frac, older):
+    """Up to about 3e4 samples the cut by launch size alone is whole rows,
+    which "seg" = 0 asks for: a checkpoint written under it, also in the older
+    form, resumes in a job of the automatic cut and ends bitwise as the
+    whole-row batch; one written under the automatic cut resumes in another
+    automatic job; another column's is refused."""
+    A = kde.KDE_METHOD_ROT | kde.KDE_METHOD_PLUGIN | kde.KDE_METHOD_LSCV
+    req = kde.Request(workloads.draw("gamma", 4099, 3, np.float32), A, 3, workloads.BATCH_GRID)
+    with kde.Context(0) as rows, kde.Context(0) as auto:
+        rows.set_option("seg", 0)
+        for src in (rows,) if older else (rows, auto):
+            want = src.batch([req])[0]
+            with kde.Job(src, req) as job:
+                _, total, _ = job.progress()
+                if frac == 1.0:
+                    job.run_to_end()
+                elif frac > 0:
+                    job.run(frac * total)
+                ck = job.checkpoint()
+            if older:
+                ck = _older(ck, 4099, workloads.BATCH_GRID[3])
+            with kde.Job(auto, req) as job2:
+                job2.resume(ck)
+                got = job2.run_to_end(total / 3)
+            assert got.status == want.status == 0
+            assert np.array_equal(got.g, want.g) and np.array_equal(got.gscale, want.gscale)
+            assert got.plugin.psi == want.plugin.psi and got.k_lscv == want.k_lscv and got.h_plugin == want.h_plugin
+        for bad_req, buf in ((kde.Request(req.x[:4000], A, 3, workloads.BATCH_GRID), ck), (req, ck[:-8])):
+            with kde.Job(auto, bad_req) as other:
+                with pytest.raises(kde.KdeError) as e:
+                    other.resume(buf)
+                assert e.value.status == kde.KDE_E_INVAL
