@@ -32,6 +32,15 @@ namespace {
 // depend on the other matrices of the call.  The mixed form rounds Z to FP32
 // (compensated 64-term runs, FP64 above the lane); both forms evaluate g at H
 // itself.  Padding samples hold +inf in the first coordinate.
+
+// four floats at any 4-byte alignment (a dimension's row starts at a multiple
+// of npad samples)
+__device__ __forceinline__ float4 load4(const float* p) {
+  float4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+
 struct HDesc {
   double logdet;  // log |H|
   int valid;      // H and G positive definite
@@ -39,14 +48,14 @@ struct HDesc {
 };
 
 // one thread per matrix (H row-major d x d, its lower triangle read): the
-// whitening map c M (row stride KDE_MAX_D) and log|H|
+// whitening map c M (row stride KDE_MAX_D, lower triangle written unless the
+// matrix is rejected) and log|H|
 __global__ void k_H_prep(const MdState* st, const double* H, int m, int f64, HDesc* out, double* Mout) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= m) return;
   const int d = st->d;
   double A[KDE_MAX_D][KDE_MAX_D], L[KDE_MAX_D][KDE_MAX_D], T[KDE_MAX_D][KDE_MAX_D];
   double* M = Mout + (int64_t)k * KDE_MAX_D * KDE_MAX_D;
-  for (int q = 0; q < KDE_MAX_D * KDE_MAX_D; ++q) M[q] = 0.0;
   HDesc o;
   o.logdet = 0.0;
   o.valid = 0;
@@ -115,73 +124,116 @@ __global__ void k_H_prep(const MdState* st, const double* H, int m, int f64, HDe
   out[k] = o;
 }
 
-// 64 consecutive j of the tile for lane i: exp2(-|z_i - z_j|^2) summed, and
-// its squares; MASK drops j <= i (the diagonal run of a wave)
-template <int D, bool MASK>
-__device__ __forceinline__ void hz_run(const float (*tile)[kBJ], int jl, int jg, const float (&zi)[D], int i,
-                                       float& a1, float& c1, float& a2, float& c2) {
-  float r1 = 0.f, r2 = 0.f;
-#pragma unroll 4
-  for (int q = 0; q < kMdRun; ++q) {
-    float s = 0.f;
+// 64 consecutive j of the tile against the lane's IB samples i, i + 64, ...:
+// exp2(-|z_i - z_j|^2) summed, and its squares; MASK drops j <= i (the
+// diagonal runs of a wave)
+template <int D, int IB, bool MASK>
+__device__ __forceinline__ void hz_run(const float (*tile)[kBJ], int jl, int jg, const float (&zi)[IB][D], int i,
+                                       float (&a1)[IB], float (&c1)[IB], float (&a2)[IB], float (&c2)[IB]) {
+  float r1[IB], r2[IB];
+#pragma unroll
+  for (int w = 0; w < IB; ++w) r1[w] = r2[w] = 0.f;
+#pragma unroll 2
+  for (int q = 0; q < kMdRun; q += 4) {
+    float zj[D][4];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      const float dd = zi[a] - tile[a][jl + q];
-      s = __builtin_fmaf(dd, dd, s);
+      const float4 v = *reinterpret_cast<const float4*>(&tile[a][jl + q]);
+      zj[a][0] = v.x;
+      zj[a][1] = v.y;
+      zj[a][2] = v.z;
+      zj[a][3] = v.w;
     }
-    if (MASK) s = (jg + q > i) ? s : __builtin_inff();
-    const float e = __builtin_amdgcn_exp2f(-s);
-    r1 += e;
-    r2 = __builtin_fmaf(e, e, r2);
+    float e[4 * IB];
+#pragma unroll
+    for (int u = 0; u < 4 * IB; ++u) {
+      float s = 0.f;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const float dd = zi[u >> 2][a] - zj[a][u & 3];
+        s = __builtin_fmaf(dd, dd, s);
+      }
+      if (MASK) s = (jg + q + (u & 3) > i + 64 * (u >> 2)) ? s : __builtin_inff();
+      e[u] = -s;
+    }
+    exp2_group(e);
+#pragma unroll
+    for (int u = 0; u < 4 * IB; ++u) {
+      r1[u >> 2] += e[u];
+      r2[u >> 2] = __builtin_fmaf(e[u], e[u], r2[u >> 2]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
-  md_fold(a1, c1, r1);
-  md_fold(a2, c2, r2);
+#pragma unroll
+  for (int w = 0; w < IB; ++w) {
+    md_fold(a1[w], c1[w], r1[w]);
+    md_fold(a2[w], c2[w], r2[w]);
+  }
 }
 
-// one block per unit of one matrix: part[2 k + {0, 1}][item] of that matrix
-template <int D>
-__global__ __launch_bounds__(kThreads) void k_HZ_units_f32(const float* __restrict__ z, int npad,
-                                                           const MdState* __restrict__ st,
-                                                           const Unit* __restrict__ units, int u0,
-                                                           double* __restrict__ part, int n_items) {
+// One block per unit of one matrix: part[2 k + {0, 1}][item] of that matrix.
+// 256 / IB lanes of IB samples i share the unit's row of 256.  IB = 2: a tile
+// read (a broadcast, whose 64 lanes' worth of data cost the LDS port as much
+// as any read) serves two pairs.  Bound: vector issue, 8.1 cycles for the
+// exponential and 2.4 for each of 2 D + 2 plain instructions a pair; with one
+// sample a lane the D reads a pair keep the LDS port of a CU busy two thirds
+// of that time.  One matrix over n = 1e5, d = 2: sweep 1008 -> 812 us (25.6
+// cycles a pair; the parts add up to 22.5).  IB = 1 where the units would not
+// fill the chip with half the waves (n = 2500, d = 2: a call of 92 us against
+// 98).
+template <int D, int IB>
+__global__ __launch_bounds__(kThreads / IB) void k_HZ_units_f32(const float* __restrict__ z, int npad,
+                                                                const MdState* __restrict__ st,
+                                                                const Unit* __restrict__ units, int u0,
+                                                                double* __restrict__ part, int n_items) {
   if (st->status != kStOk) return;
   const Unit u = units[u0 + blockIdx.x];
   const int n = st->n;
-  __shared__ float tile[D][kBJ];
-  __shared__ double red[4][2];
+  constexpr int T = kThreads / IB, W = T / 64;
+  __shared__ __attribute__((aligned(16))) float tile[D][kBJ];
+  __shared__ double red[2][W];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int row0 = u.row * kBI;
-  const int i = row0 + tid;
-  float zi[D];
+  const int wave_i0 = u.row * kBI + wave * 64 * IB;
+  const int i = wave_i0 + lane;
+  float zi[IB][D], a1[IB], c1[IB], a2[IB], c2[IB];
 #pragma unroll
-  for (int a = 0; a < D; ++a) zi[a] = (i < n) ? z[(int64_t)a * npad + i] : 0.f;
-  const int wave_i0 = row0 + wave * 64;
-  float a1 = 0.f, c1 = 0.f, a2 = 0.f, c2 = 0.f;
-  for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+  for (int w = 0; w < IB; ++w) {
+#pragma unroll
+    for (int a = 0; a < D; ++a) zi[w][a] = (i + 64 * w < n) ? z[(int64_t)a * npad + i + 64 * w] : 0.f;
+    a1[w] = c1[w] = a2[w] = c2[w] = 0.f;
+  }
+  const int j_end = min(u.j_end, (n + kMdRun - 1) / kMdRun * kMdRun);
+  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+    const int te = min(t0 + kBJ, j_end);
     __syncthreads();
+#pragma unroll
     for (int a = 0; a < D; ++a)
-      for (int q = tid; q < kBJ; q += kThreads) tile[a][q] = z[(int64_t)a * npad + t0 + q];
+      for (int q = 4 * tid; q < te - t0; q += 4 * T)
+        *reinterpret_cast<float4*>(&tile[a][q]) = load4(z + (int64_t)a * npad + t0 + q);
     __syncthreads();
-    int js = max(t0, wave_i0);
-    const int te = t0 + kBJ;
-    if (js < te) {
-      if (js == wave_i0) {
-        hz_run<D, true>(tile, js - t0, js, zi, i, a1, c1, a2, c2);
-        js += kMdRun;
-      }
-      for (; js < te; js += kMdRun) hz_run<D, false>(tile, js - t0, js, zi, i, a1, c1, a2, c2);
+    for (int js = max(t0, wave_i0); js < te; js += kMdRun) {
+      if (js < wave_i0 + 64 * IB)
+        hz_run<D, IB, true>(tile, js - t0, js, zi, i, a1, c1, a2, c2);
+      else
+        hz_run<D, IB, false>(tile, js - t0, js, zi, i, a1, c1, a2, c2);
     }
   }
-  const bool valid = i < n;
-  const double v1 = md_wave_sum(valid ? (double)a1 - (double)c1 : 0.0);
-  const double v2 = md_wave_sum(valid ? (double)a2 - (double)c2 : 0.0);
-  if (lane == 0) {
-    red[wave][0] = v1;
-    red[wave][1] = v2;
-  }
+  double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+  for (int w = 0; w < IB; ++w)
+    if (i + 64 * w < n) {
+      s1 += (double)a1[w] - (double)c1[w];
+      s2 += (double)a2[w] - (double)c2[w];
+    }
+  const double v = wave_sum2(s1, s2);
+  if ((lane & 31) == 0) red[lane >> 5][wave] = v;
   __syncthreads();
-  if (tid < 2) part[(int64_t)tid * n_items + u.item] = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+  if (tid < 2) {
+    double s = red[tid][0];
+    for (int w = 1; w < W; ++w) s += red[tid][w];
+    part[(int64_t)tid * n_items + u.item] = s;
+  }
 }
 
 // The same sweep for wide samples (D = 8, 16), where the LDS reads of the
@@ -194,18 +246,27 @@ template <int D, bool MASK>
 __device__ __forceinline__ void hz_run_s(const float* __restrict__ z, int npad, int jg, const float (&zi)[D], int i,
                                        float& a1, float& c1, float& a2, float& c2) {
   float r1 = 0.f, r2 = 0.f;
-#pragma unroll 8
-  for (int q = 0; q < kMdRun; ++q) {
-    float s = 0.f;
+#pragma unroll 2
+  for (int q = 0; q < kMdRun; q += kExpGroup) {
+    float e[kExpGroup];
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      const float dd = zi[a] - z[(int64_t)a * npad + jg + q];
-      s = __builtin_fmaf(dd, dd, s);
+    for (int u = 0; u < kExpGroup; ++u) {
+      float s = 0.f;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        const float dd = zi[a] - z[(int64_t)a * npad + jg + q + u];
+        s = __builtin_fmaf(dd, dd, s);
+      }
+      if (MASK) s = (jg + q + u > i) ? s : __builtin_inff();
+      e[u] = -s;
     }
-    if (MASK) s = (jg + q > i) ? s : __builtin_inff();
-    const float e = __builtin_amdgcn_exp2f(-s);
-    r1 += e;
-    r2 = __builtin_fmaf(e, e, r2);
+    exp2_group(e);
+#pragma unroll
+    for (int u = 0; u < kExpGroup; ++u) {
+      r1 += e[u];
+      r2 = __builtin_fmaf(e[u], e[u], r2);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
   md_fold(a1, c1, r1);
   md_fold(a2, c2, r2);
@@ -270,7 +331,7 @@ __global__ __launch_bounds__(kThreads) void k_HZ_units_f64(const double* __restr
     for (int a = 0; a < D; ++a)
       for (int q = tid; q < kT; q += kThreads) tile[a][q] = z[(int64_t)a * npad + t0 + q];
     __syncthreads();
-    const int qa = max(0, i + 1 - t0), qb = min(kT, n - t0);
+    const int qa = max(0, i + 1 - t0), qb = min(kT, min(n, u.j_end) - t0);
     for (int q = qa; q < qb; ++q) {
       double s = 0.0;
 #pragma unroll
@@ -320,6 +381,10 @@ __global__ void k_H_final(const MdState* st, const HDesc* hd, int m, const doubl
   gs[k] = 2.0 / (n * n) * (A * sums[2 * k] + 2.0 * B * sums[2 * k + 1]) + R / n;
 }
 
+// Two samples a lane from as many items as fill the chip's 8192 waves (8 a
+// SIMD) with their two waves each.
+constexpr int kIB2Items = 4096;
+
 void launch_HZ(hipStream_t s, int D, bool f64, const float* z32, const double* z64, int npad, const MdState* st,
                const Unit* units, int u0, int cnt, double* part, int n_items) {
 #define KDE_HZ_CASE(DD)                                                                                  \
@@ -327,8 +392,10 @@ void launch_HZ(hipStream_t s, int D, bool f64, const float* z32, const double* z
     k_HZ_units_f64<DD><<<cnt, kThreads, 0, s>>>(z64, npad, st, units, u0, part, n_items);                \
   else if constexpr (DD >= 8)                                                                            \
     k_HZ_units_f32s<DD><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);               \
+  else if (n_items >= kIB2Items)                                                                         \
+    k_HZ_units_f32<DD, 2><<<cnt, kThreads / 2, 0, s>>>(z32, npad, st, units, u0, part, n_items);         \
   else                                                                                                   \
-    k_HZ_units_f32<DD><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);                \
+    k_HZ_units_f32<DD, 1><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);             \
   return
   switch (D) {
     case 2: KDE_HZ_CASE(2);
