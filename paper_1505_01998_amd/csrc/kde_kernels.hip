@@ -1314,6 +1314,7 @@ __global__ __launch_bounds__(kThreads) void k_reduce_rows(const RowDesc* __restr
   __shared__ double sh[kThreads];
   const RowDesc r = rows[blockIdx.x];
   double s = 0.0;
+#pragma unroll 8
   for (int c = threadIdx.x; c < r.n; c += kThreads) s += r.src[c];
   s = block_sum(s, sh);
   if (threadIdx.x == 0) *r.dst = s;

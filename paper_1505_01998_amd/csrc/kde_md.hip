@@ -53,15 +53,20 @@ __global__ __launch_bounds__(kThreads) void k_md_sum(const void* raw, int f64, i
   if (threadIdx.x == 0) nf[blockIdx.x] = (int)nb;
 }
 
+// one wave: lane a the mean of coordinate a (blocks in order), lane 63 the rest
 __global__ void k_md_mean(const double* part, const int* nf, int nblk, int n, int d, MdState* st) {
-  if (threadIdx.x != 0) return;
-  st->d = d;
-  st->n = n;
-  int bad = 0;
-  for (int b = 0; b < nblk; ++b) bad += nf[b];
-  st->status = bad ? kStInval : kStOk;
-  for (int a = 0; a < d; ++a) {
+  const int a = threadIdx.x;
+  if (a == 63) {
+    st->d = d;
+    st->n = n;
+    int bad = 0;
+#pragma unroll 8
+    for (int b = 0; b < nblk; ++b) bad += nf[b];
+    st->status = bad ? kStInval : kStOk;
+  }
+  if (a < d) {
     double s = 0.0;
+#pragma unroll 8
     for (int b = 0; b < nblk; ++b) s += part[b * KDE_MAX_D + a];
     st->mean[a] = s / (double)n;
   }
@@ -84,18 +89,23 @@ __global__ __launch_bounds__(kThreads) void k_md_cov(const void* raw, int f64, i
     }
 }
 
-// one thread: Sigma, its Cholesky factor, log|Sigma| and L^-1
-__global__ void k_md_factor(const double* part, int nblk, MdState* st) {
-  if (threadIdx.x != 0 || st->status != kStOk) return;
+// Sigma, a thread an entry (blocks in order); then one thread: its Cholesky
+// factor, log|Sigma| and L^-1
+__global__ __launch_bounds__(KDE_MAX_D* KDE_MAX_D) void k_md_factor(const double* part, int nblk, MdState* st) {
+  if (st->status != kStOk) return;
   const int d = st->d;
-  double S[KDE_MAX_D][KDE_MAX_D], L[KDE_MAX_D][KDE_MAX_D];
-  for (int a = 0; a < d; ++a)
-    for (int b = 0; b <= a; ++b) {
-      double s = 0.0;
-      for (int k = 0; k < nblk; ++k) s += part[k * KDE_MAX_D * KDE_MAX_D + a * KDE_MAX_D + b];
-      S[a][b] = S[b][a] = s / (double)(st->n - 1);
-      st->sigma[a * KDE_MAX_D + b] = st->sigma[b * KDE_MAX_D + a] = S[a][b];
-    }
+  __shared__ double S[KDE_MAX_D][KDE_MAX_D];
+  double L[KDE_MAX_D][KDE_MAX_D];
+  const int ta = threadIdx.x / KDE_MAX_D, tb = threadIdx.x % KDE_MAX_D;
+  if (ta < d && tb <= ta) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < nblk; ++k) s += part[k * KDE_MAX_D * KDE_MAX_D + ta * KDE_MAX_D + tb];
+    S[ta][tb] = S[tb][ta] = s / (double)(st->n - 1);
+    st->sigma[ta * KDE_MAX_D + tb] = st->sigma[tb * KDE_MAX_D + ta] = S[ta][tb];
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   for (int a = 0; a < d; ++a)
     for (int b = 0; b < d; ++b) L[a][b] = 0.0;
   for (int a = 0; a < d; ++a)
@@ -175,11 +185,36 @@ __global__ __launch_bounds__(kThreads) void k_md_prep(const MdState* st, const d
   }
 }
 
-template <int D, int HC, bool MASK>
-__device__ __forceinline__ void md_run(const float (*tile)[kBJ], int jl, int jg, const float (&yi)[D], int i,
-                                       const float (&ck)[HC], float (&a1)[HC], float (&c1)[HC], float (&a2)[HC],
-                                       float (&c2)[HC]) {
-  float r1[HC], r2[HC];
+// One pair's squared distance s against the HC bandwidths, in groups of
+// exponentials as in the univariate sweep (bound: vector issue, as there): n =
+// 4e4, d = 3, 64 bandwidths in units of 256 samples 8.6 -> 7.8 ms.
+template <int HC>
+__device__ __forceinline__ void md_terms(float s, const float (&ck)[HC], float (&r1)[HC], float (&r2)[HC]) {
+#pragma unroll
+  for (int k0 = 0; k0 < HC; k0 += kExpGroup) {
+    float e[kExpGroup];
+#pragma unroll
+    for (int k = 0; k < kExpGroup; ++k) e[k] = s * ck[k0 + k];
+    exp2_group(e);
+#pragma unroll
+    for (int k = 0; k < kExpGroup; ++k) {
+      r1[k0 + k] += e[k];
+      r2[k0 + k] = __builtin_fmaf(e[k], e[k], r2[k0 + k]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The plain sums of one run: 64 consecutive j against the lane's sample, for
+// the HC bandwidths; MASK drops j <= i (the diagonal run of a wave).  Up to
+// D = 4 the j coordinates come from an LDS tile (broadcast reads of TJ-long
+// rows); for wider samples D reads a pair would limit the sweep, and the
+// coordinates, the same for every lane of a wave, are read with uniform
+// addresses (scalar loads through the scalar cache).
+template <int D, int HC, int TJ, bool MASK>
+__device__ __forceinline__ void md_run(const float (*tile)[TJ], int jl, const float* __restrict__ y, int npad, int jg,
+                                       const float (&yi)[D], int i, const float (&ck)[HC], float (&r1)[HC],
+                                       float (&r2)[HC]) {
 #pragma unroll
   for (int k = 0; k < HC; ++k) r1[k] = r2[k] = 0.f;
 #pragma unroll 2
@@ -187,17 +222,17 @@ __device__ __forceinline__ void md_run(const float (*tile)[kBJ], int jl, int jg,
     float s = 0.f;
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      const float dd = yi[a] - tile[a][jl + q];
+      const float dd = yi[a] - (D >= 8 ? y[(int64_t)a * npad + jg + q] : tile[a][jl + q]);
       s = __builtin_fmaf(dd, dd, s);
     }
     if (MASK) s = (jg + q > i) ? s : __builtin_inff();
-#pragma unroll
-    for (int k = 0; k < HC; ++k) {
-      const float e = __builtin_amdgcn_exp2f(s * ck[k]);
-      r1[k] += e;
-      r2[k] = __builtin_fmaf(e, e, r2[k]);
-    }
+    md_terms<HC>(s, ck, r1, r2);
   }
+}
+
+template <int HC>
+__device__ __forceinline__ void md_fold_run(const float (&r1)[HC], const float (&r2)[HC], float (&a1)[HC],
+                                            float (&c1)[HC], float (&a2)[HC], float (&c2)[HC]) {
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
     md_fold(a1[k], c1[k], r1[k]);
@@ -205,36 +240,92 @@ __device__ __forceinline__ void md_run(const float (*tile)[kBJ], int jl, int jg,
   }
 }
 
-// md_run for wide samples (D = 8, 16): the j coordinates are the same for
-// every lane of a wave, so they are read with uniform addresses (scalar loads
-// through the scalar cache) instead of from an LDS tile
-template <int D, int HC, bool MASK>
-__device__ __forceinline__ void md_run_s(const float* __restrict__ y, int npad, int jg, const float (&yi)[D],
-                                         int i, const float (&ck)[HC], float (&a1)[HC], float (&c1)[HC],
-                                         float (&a2)[HC], float (&c2)[HC]) {
-  float r1[HC], r2[HC];
+// One unit of a pass of few units: 64 samples i (one per lane of every wave)
+// against the unit's j-range, by the eight waves of a block, a run of 64 j a
+// wave and step.  The waves exchange their runs' sums through LDS and each
+// folds, run by run in ascending j, the sums of its HC / 8 bandwidths: the
+// folds are those of one wave walking the whole j-range, as in
+// k_md_units_f32 (the compensated sums depend on where a range is cut: a
+// finer cut moved g by up to 1.2e-9).  A call against units of 256 samples:
+// n = 4e4, d = 3, 64 bandwidths 7.99 -> 5.81 ms (9.0e12 terms/s); n = 4000,
+// d = 2, 150 1.03 -> 0.34 ms; n = 2e4, d = 5, 32 3.9 -> 1.2 ms.
+constexpr int kMdWaves = 8;
+constexpr int kMdWideThreads = 64 * kMdWaves;
+
+template <int D, int HC>
+__global__ __launch_bounds__(kMdWideThreads) __attribute__((amdgpu_waves_per_eu(HC > 8 ? 4 : 8))) void k_md_wide_f32(
+    const float* __restrict__ y, int npad, const MdState* __restrict__ st, const float* __restrict__ c32,
+    const Unit* __restrict__ units, int u0, double* __restrict__ part, int n_items, int n_h) {
+  if (st->status != kStOk) return;
+  const Unit u = units[u0 + blockIdx.x];
+  const int n = st->n;
+  constexpr int V = 2 * HC / kMdWaves;  // sums a wave folds: S1, S2 of HC / 8 bandwidths
+  constexpr int TJ = kMdWideThreads;
+  typedef float vrun __attribute__((ext_vector_type(V)));
+  __shared__ __attribute__((aligned(16))) float tile[D < 8 ? D : 1][TJ];
+  __shared__ vrun sums[kMdWaves][kMdWaves][64];  // [run][folding wave][lane]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i0 = u.row * 64;
+  const int i = i0 + lane;
+  float yi[D], ck[HC];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) r1[k] = r2[k] = 0.f;
-#pragma unroll 2
-  for (int q = 0; q < kMdRun; ++q) {
-    float s = 0.f;
+  for (int a = 0; a < D; ++a) yi[a] = (i < n) ? y[(int64_t)a * npad + i] : 0.f;
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      const float dd = yi[a] - y[(int64_t)a * npad + jg + q];
-      s = __builtin_fmaf(dd, dd, s);
+  for (int k = 0; k < HC; ++k)
+    ck[k] = __builtin_bit_cast(float,
+                               __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, c32[u.chunk * HC + k])));
+  float acc[V], comp[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) acc[v] = comp[v] = 0.f;
+  const int j_begin = max(u.j_begin, i0), j_end = min(u.j_end, (n + kMdRun - 1) / kMdRun * kMdRun);
+  for (int t0 = j_begin; t0 < j_end; t0 += TJ) {
+    // every wave has swept the tile before (the second barrier below)
+    if (D < 8 && t0 + tid < j_end) {
+#pragma unroll
+      for (int a = 0; a < (D < 8 ? D : 1); ++a) tile[a][tid] = y[(int64_t)a * npad + t0 + tid];
     }
-    if (MASK) s = (jg + q > i) ? s : __builtin_inff();
+    __syncthreads();  // the tile stands; every wave has folded the runs before
+    const int js = __builtin_amdgcn_readfirstlane(t0 + wave * kMdRun);
+    if (js < j_end) {
+      float r1[HC], r2[HC];
+      if (js == i0)
+        md_run<D, HC, TJ, true>(tile, wave * kMdRun, y, npad, js, yi, i, ck, r1, r2);
+      else
+        md_run<D, HC, TJ, false>(tile, wave * kMdRun, y, npad, js, yi, i, ck, r1, r2);
 #pragma unroll
-    for (int k = 0; k < HC; ++k) {
-      const float e = __builtin_amdgcn_exp2f(s * ck[k]);
-      r1[k] += e;
-      r2[k] = __builtin_fmaf(e, e, r2[k]);
+      for (int w = 0; w < kMdWaves; ++w) {
+        vrun o;
+#pragma unroll
+        for (int v = 0; v < V; v += 2) {
+          o[v] = r1[w * (V / 2) + v / 2];
+          o[v + 1] = r2[w * (V / 2) + v / 2];
+        }
+        sums[wave][w][lane] = o;
+      }
+    }
+    __syncthreads();
+    const int runs = min(kMdWaves, (j_end - t0) / kMdRun);
+    for (int r = 0; r < runs; ++r) {
+      const vrun o = sums[r][wave][lane];
+#pragma unroll
+      for (int v = 0; v < V; ++v) md_fold(acc[v], comp[v], o[v]);
     }
   }
+  double v[V];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) {
-    md_fold(a1[k], c1[k], r1[k]);
-    md_fold(a2[k], c2[k], r2[k]);
+  for (int q = 0; q < V; ++q) v[q] = (i < n) ? (double)acc[q] - (double)comp[q] : 0.0;
+  // row q of the chunk's 2 HC sums: S1, S2 of each bandwidth in turn
+  auto put = [&](int q, double s) {
+    const int hh = u.chunk * HC + q / 2;
+    if (hh < n_h) part[(int64_t)(2 * hh + (q & 1)) * n_items + u.item] = s;
+  };
+  if constexpr (V == 4) {
+    const double s = row16_sum(swap16_add(swap32_add(v[0], v[2]), swap32_add(v[1], v[3])));
+    if ((lane & 15) == 0) put(wave * V + (lane >> 4), s);
+  } else {
+    const double s = wave_sum2(v[0], v[1]);
+    if ((lane & 31) == 0) put(wave * V + (lane >> 5), s);
   }
 }
 
@@ -256,50 +347,58 @@ __global__ __launch_bounds__(kThreads) void k_md_units_f32(const float* __restri
 #pragma unroll
   for (int a = 0; a < D; ++a) yi[a] = (i < n) ? y[(int64_t)a * npad + i] : 0.f;
   const int wave_i0 = __builtin_amdgcn_readfirstlane(row0 + wave * 64);
-  float ck[HC], a1[HC], c1[HC], a2[HC], c2[HC];
+  float ck[HC], a1[HC], c1[HC], a2[HC], c2[HC], r1[HC], r2[HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    ck[k] = c32[u.chunk * HC + k];
+    ck[k] = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
+                                          __builtin_bit_cast(int, c32[u.chunk * HC + k])));
     a1[k] = c1[k] = a2[k] = c2[k] = 0.f;
   }
+  // the runs of 64 that hold a sample
+  const int j_end = min(u.j_end, (n + kMdRun - 1) / kMdRun * kMdRun);
   if constexpr (D >= 8) {
-    // wide samples: D tile reads a pair would limit the sweep; read the j
-    // coordinates with uniform addresses instead (no tile, no barrier)
+    // no tile, no barrier
     int js = __builtin_amdgcn_readfirstlane(max(u.j_begin, wave_i0));
-    const int je = __builtin_amdgcn_readfirstlane(u.j_end);
+    const int je = __builtin_amdgcn_readfirstlane(j_end);
     if (js < je && js == wave_i0) {
-      md_run_s<D, HC, true>(y, npad, js, yi, i, ck, a1, c1, a2, c2);
+      md_run<D, HC, kBJ, true>(nullptr, 0, y, npad, js, yi, i, ck, r1, r2);
+      md_fold_run<HC>(r1, r2, a1, c1, a2, c2);
       js += kMdRun;
     }
-    for (; js < je; js += kMdRun) md_run_s<D, HC, false>(y, npad, js, yi, i, ck, a1, c1, a2, c2);
+    for (; js < je; js += kMdRun) {
+      md_run<D, HC, kBJ, false>(nullptr, 0, y, npad, js, yi, i, ck, r1, r2);
+      md_fold_run<HC>(r1, r2, a1, c1, a2, c2);
+    }
   } else {
     __shared__ float tile[D][kBJ];
-    for (int t0 = u.j_begin; t0 < u.j_end; t0 += kBJ) {
+    for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
+      const int te = min(t0 + kBJ, j_end);
       __syncthreads();
       for (int a = 0; a < D; ++a)
-        for (int q = tid; q < kBJ; q += kThreads) tile[a][q] = y[(int64_t)a * npad + t0 + q];
+        for (int q = tid; q < te - t0; q += kThreads) tile[a][q] = y[(int64_t)a * npad + t0 + q];
       __syncthreads();
       int js = max(t0, wave_i0);
-      const int te = t0 + kBJ;
       if (js < te) {
         if (js == wave_i0) {
-          md_run<D, HC, true>(tile, js - t0, js, yi, i, ck, a1, c1, a2, c2);
+          md_run<D, HC, kBJ, true>(tile, js - t0, y, npad, js, yi, i, ck, r1, r2);
+          md_fold_run<HC>(r1, r2, a1, c1, a2, c2);
           js += kMdRun;
         }
-        for (; js < te; js += kMdRun) md_run<D, HC, false>(tile, js - t0, js, yi, i, ck, a1, c1, a2, c2);
+        for (; js < te; js += kMdRun) {
+          md_run<D, HC, kBJ, false>(tile, js - t0, y, npad, js, yi, i, ck, r1, r2);
+          md_fold_run<HC>(r1, r2, a1, c1, a2, c2);
+        }
       }
     }
   }
   const bool valid = i < n;
+  double v[2 * HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    const double v1 = md_wave_sum(valid ? (double)a1[k] - (double)c1[k] : 0.0);
-    const double v2 = md_wave_sum(valid ? (double)a2[k] - (double)c2[k] : 0.0);
-    if (lane == 0) {
-      red[wave][2 * k] = v1;
-      red[wave][2 * k + 1] = v2;
-    }
+    v[2 * k] = valid ? (double)a1[k] - (double)c1[k] : 0.0;
+    v[2 * k + 1] = valid ? (double)a2[k] - (double)c2[k] : 0.0;
   }
+  wave_sums(v, red[wave], lane);
   __syncthreads();
   if (tid < 2 * HC) {
     const int hh = u.chunk * HC + (tid >> 1);
@@ -337,10 +436,11 @@ __global__ __launch_bounds__(kThreads) void k_md_units_f64(const double* __restr
   }
   for (int t0 = u.j_begin; t0 < u.j_end; t0 += kT) {
     __syncthreads();
+    const int len = min(kT, u.j_end - t0);
     for (int a = 0; a < D; ++a)
-      for (int q = tid; q < kT; q += kThreads) tile[a][q] = y[(int64_t)a * npad + t0 + q];
+      for (int q = tid; q < len; q += kThreads) tile[a][q] = y[(int64_t)a * npad + t0 + q];
     __syncthreads();
-    for (int q = 0; q < kT; ++q) {
+    for (int q = 0; q < len; ++q) {
       const int j = t0 + q;
       if (j <= i) continue;
       double s = 0.0;
@@ -358,15 +458,13 @@ __global__ __launch_bounds__(kThreads) void k_md_units_f64(const double* __restr
     }
   }
   const bool valid = i < n;
+  double v[2 * HC];
 #pragma unroll
   for (int k = 0; k < HC; ++k) {
-    const double v1 = md_wave_sum(valid ? s1[k] : 0.0);
-    const double v2 = md_wave_sum(valid ? s2[k] : 0.0);
-    if (lane == 0) {
-      red[wave][2 * k] = v1;
-      red[wave][2 * k + 1] = v2;
-    }
+    v[2 * k] = valid ? s1[k] : 0.0;
+    v[2 * k + 1] = valid ? s2[k] : 0.0;
   }
+  wave_sums(v, red[wave], lane);
   __syncthreads();
   if (tid < 2 * HC) {
     const int hh = u.chunk * HC + (tid >> 1);
@@ -441,12 +539,15 @@ __global__ __launch_bounds__(1024) void k_md_finalize(MdState* st, const double*
   }
 }
 
+// HC = 4: the FP64 form
 template <int D, int HC>
-void launch_md_units(hipStream_t s, bool f64, const float* y32, const double* y64, int npad, const MdState* st,
+void launch_md_units(hipStream_t s, bool wide, const float* y32, const double* y64, int npad, const MdState* st,
                      const float* c32, const double* c64, const Unit* units, int u0, int cnt, double* part,
                      int n_items, int n_h) {
-  if (f64)
+  if constexpr (HC == 4)
     k_md_units_f64<D, HC><<<cnt, kThreads, 0, s>>>(y64, npad, st, c64, units, u0, part, n_items, n_h);
+  else if (wide)
+    k_md_wide_f32<D, HC><<<cnt, kMdWideThreads, 0, s>>>(y32, npad, st, c32, units, u0, part, n_items, n_h);
   else
     k_md_units_f32<D, HC><<<cnt, kThreads, 0, s>>>(y32, npad, st, c32, units, u0, part, n_items, n_h);
 }
@@ -454,11 +555,11 @@ void launch_md_units(hipStream_t s, bool f64, const float* y32, const double* y6
 // bandwidths per block: fewer for wide samples (registers)
 int md_hc(int D, bool f64) { return f64 ? 4 : (D <= 4 ? 16 : 8); }
 
-void launch_md(hipStream_t s, int D, bool f64, const float* y32, const double* y64, int npad, const MdState* st,
+void launch_md(hipStream_t s, int D, bool f64, bool wide, const float* y32, const double* y64, int npad, const MdState* st,
                const float* c32, const double* c64, const Unit* units, int u0, int cnt, double* part, int n_items,
                int n_h) {
 #define KDE_MD_CASE(DD, HH)                                                                                  \
-  launch_md_units<DD, HH>(s, f64, y32, y64, npad, st, c32, c64, units, u0, cnt, part, n_items, n_h);          \
+  launch_md_units<DD, HH>(s, wide, y32, y64, npad, st, c32, c64, units, u0, cnt, part, n_items, n_h);          \
   return
   if (f64) {
     switch (D) {
@@ -504,7 +605,7 @@ void md_stage(hipStream_t st, const void* raw, bool raw_f64, int n, int d, int D
   k_md_sum<<<nblk, kThreads, 0, st>>>(raw, fx, n, d, nblk, ps, nf);
   k_md_mean<<<1, 64, 0, st>>>(ps, nf, nblk, n, d, dst);
   k_md_cov<<<nblk, kThreads, 0, st>>>(raw, fx, n, d, nblk, dst, pc);
-  k_md_factor<<<1, 64, 0, st>>>(pc, nblk, dst);
+  k_md_factor<<<1, KDE_MAX_D * KDE_MAX_D, 0, st>>>(pc, nblk, dst);
   k_md_whiten<<<(npad + kThreads - 1) / kThreads, kThreads, 0, st>>>(raw, fx, n, D, npad, dst, dst->linv, y32,
                                                                      y64);
 }
@@ -535,15 +636,25 @@ static kde_status run_md(kde_ctx* c, const kde_matrix& x, const double* h_grid, 
   const int nblk = std::min(kMdBlocks, std::max(1, (n + 2047) / 2048));
   // work items as the univariate planner cuts the triangle
   ColItems items;
-  make_items(n, capped_seg(c, n, kSegRefHC, (double)chunks), items);
-  const int n_items = (int)items.pairs.size();
+  // (the FP64 form cut until a pass fills the chip; the mixed form by launch
+  // size alone, in units of 64 samples i where those of 256 would be few:
+  // n = 4e4, 64 bandwidths are 1000 of the 1024 blocks the chip holds)
+  const Split cut = f64 ? pick_split(c, n, (double)chunks, kFillLscv)
+                        : Split{capped_seg(c, n, kSegRefHC, (double)chunks), 1};
+  make_items(n, cut.pieces > 1 ? kBJ / cut.pieces : cut.seg, items);
+  const bool wide = !f64 && items.pairs.size() * (size_t)chunks < 8192;
+  const int groups = wide ? kBI / 64 : 1;
+  const int n_items = (int)items.pairs.size() * groups;
   std::vector<Unit> units;
   std::vector<double> cost, ev;  // planning cost, pair-term evaluations
   for (int it = 0; it < n_items; ++it)
     for (int ch = 0; ch < chunks; ++ch) {
-      units.push_back(Unit{0, items.row[it], items.jb[it], items.je[it], it, ch});
-      cost.push_back(items.pairs[it] * std::min(hc, n_h - ch * hc) * (1.0 + 2.0 * D / hc));
-      ev.push_back(items.pairs[it] * std::min(hc, n_h - ch * hc));
+      const int k = it / groups, row = items.row[k] * groups + it % groups;
+      const double pairs =
+          wide ? row_pairs(n, (int64_t)row * 64, 64, items.jb[k], items.je[k]) : items.pairs[k];
+      units.push_back(Unit{0, row, items.jb[k], items.je[k], it, ch});
+      cost.push_back(pairs * std::min(hc, n_h - ch * hc) * (1.0 + 2.0 * D / hc));
+      ev.push_back(pairs * std::min(hc, n_h - ch * hc));
     }
   std::vector<RowDesc> rows;
   // device layout
@@ -590,7 +701,7 @@ static kde_status run_md(kde_ctx* c, const kde_matrix& x, const double* h_grid, 
     kde_ctx::Pending pd{nullptr, nullptr, kFamMd, 0.0};
     for (size_t u = u0; u < u1; ++u) pd.evals += ev[u];
     if ((s = timed_begin(c, pd))) return s;
-    launch_md(st, D, f64, y32, y64, npad, dst, (const float*)(b + o_c32), (const double*)(b + o_c64),
+    launch_md(st, D, f64, wide, y32, y64, npad, dst, (const float*)(b + o_c32), (const double*)(b + o_c64),
               (const Unit*)(b + o_units), (int)u0, (int)(u1 - u0), part, n_items, n_h);
     if ((s = timed_end(c, pd))) return s;
     u0 = u1;

@@ -290,6 +290,8 @@ int64_t pick_seg(const kde_ctx* c, int64_t n, int hc);
 constexpr double kMaxUnits = 16777216.0;
 // pick_seg, lengthened while items x chunks would exceed kMaxUnits.
 int64_t capped_seg(const kde_ctx* c, int64_t n, int hc, double chunks);
+// Pairs i < j with i in [i0, i0 + rows), j in [jb, je), both < n.
+double row_pairs(int64_t n, int64_t i0, int64_t rows, int64_t jb, int64_t je);
 // How a pass over one column is cut: item length (0: whole rows) and the
 // pieces each item is cut into along j.
 struct Split {

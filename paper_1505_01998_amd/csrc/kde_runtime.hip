@@ -119,8 +119,6 @@ std::string check_grid(const kde_grid& g) {
 }
 
 // ---- work items
-double row_pairs(int64_t n, int64_t i0, int64_t rows, int64_t jb, int64_t je);
-
 // Pairs i < j with i in the row's samples, j in [jb, je), both < n:
 // sum over i of max(0, je - max(jb, i + 1)) in closed form (rows i < jb
 // contribute je - jb each, rows i >= jb the arithmetic series je - 1 - i).

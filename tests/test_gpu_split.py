@@ -105,3 +105,25 @@ def test_checkpoint_of_the_cut_by_launch_size_resumes(kde, frac, older):
                 with pytest.raises(kde.KdeError) as e:
                     other.resume(buf)
                 assert e.value.status == kde.KDE_E_INVAL
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("n,d", [(5, 2), (63, 3), (64, 2), (65, 4), (127, 2), (128, 1), (129, 3), (255, 2), (257, 4),
+                                 (513, 2), (1281, 3), (700, 6)])
+def test_d_dimensional_sweeps_at_the_edges(kde, precision, n, d):
+    """LSCV_h and LSCV_H around a run, a wave's two samples a lane, a row and
+    a tile: g within 1e-5 (mixed) and 1e-10 (FP64) of its scale."""
+    x = workloads.draw_matrix(n, d, 40 + n, np.float32 if precision == "mixed" else np.float64)
+    tol = 1e-5 if precision == "mixed" else 1e-10
+    grid = np.geomspace(0.2, 2.0, 19)
+    S = np.atleast_2d(np.cov(x.astype(np.float64), rowvar=False))
+    with kde.Context(0, precision) as c:
+        g, gs, _ = c.lscv_md_curve(x, grid)
+        H = np.stack([0.3 * S, 0.05 * np.diag(np.diag(S))])
+        gH, gsH = c.lscv_H_eval(x, H)
+        one = [c.lscv_H_prepare(x).eval(h)[0][0] for h in H]
+    o = oracle.lscv_md_curve(x, grid)
+    assert np.all(np.abs(g - o.g) <= tol * o.gscale)
+    for k in range(2):
+        assert abs(gH[k] - oracle.lscv_H(x, H[k])) <= tol * gsH[k]
+    assert np.array_equal(one, gH)
