@@ -25,6 +25,10 @@ constexpr int kPad = kBJ + kBI;
 // min(kStatBlocks, ceil(n / 2048)) of them).
 constexpr int kStatBlocks = 1024;
 
+// Tile pruning: the skipped share of every pair sum is below this fraction
+// of the sum (2^-34).
+constexpr double kPruneEps = 5.820766091346741e-11;
+
 // Status values written by device code (same numbers as kde_status).
 constexpr int kStOk = 0;
 constexpr int kStInval = 1;

@@ -153,10 +153,6 @@ struct JobGraph {
 };
 
 constexpr size_t kMaxGraphs = 8;
-// Tile pruning: the skipped share of every pair sum is below this fraction
-// of the sum (2^-34).
-constexpr double kPruneEps = 5.820766091346741e-11;
-
 // Variant of the LSCV pass chosen by the tile autotuner for one shape.
 // Variants of the persistent dense LSCV sweep the autotuner chooses among:
 // (bandwidths per block, samples per LDS tile); index 2 is the default.

@@ -127,3 +127,26 @@ def test_d_dimensional_sweeps_at_the_edges(kde, precision, n, d):
     for k in range(2):
         assert abs(gH[k] - oracle.lscv_H(x, H[k])) <= tol * gsH[k]
     assert np.array_equal(one, gH)
+
+
+@pytest.mark.parametrize("hc", [8, 16, 32])
+@pytest.mark.parametrize("n,n_h", [(300, 17), (2049, 9), (5003, 40), (12000, 100)])
+def test_pruned_parts_of_a_chunk(kde, hc, n, n_h):
+    """The pruned sweep leaves out parts of a bandwidth chunk run by run: every
+    sum within 2^-34 of the dense one, and 1e-6 for the order of the samples
+    (two clusters, so that runs of every part are left out); the count of
+    evaluations is whole and no larger than with whole chunks."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    x = np.concatenate([rng.normal(0, 1, n // 2), rng.normal(9, 0.3, n - n // 2)]).astype(np.float32)
+    rng.shuffle(x)
+    grid = np.geomspace(0.002, 1.5, n_h)
+    req = kde.Request(x, kde.KDE_METHOD_LSCV, 2, grid)
+    with kde.Context(0) as dense, kde.Context(0) as pr:
+        pr.set_option("lscv_hc", hc)
+        pr.set_option("prune", 1)
+        sd, sp = dense.lscv_sums(x, grid), pr.lscv_sums(x, grid)
+        a, b = dense.batch([req])[0], pr.batch([req])[0]
+    for u, v in zip(sd, sp):
+        assert np.all(np.abs(u - v) <= (1e-6 + 2.0**-34) * u + n * n * 2.0**-126)
+    assert b.lscv_evals == int(b.lscv_evals) and 0 < b.lscv_evals < a.lscv_evals
+    assert a.k_lscv == b.k_lscv
