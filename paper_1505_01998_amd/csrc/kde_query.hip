@@ -56,6 +56,27 @@ __device__ __forceinline__ double block_sum_q(double v, double* sh) {
   return r;
 }
 
+// exp2(cf (x - X)^2) over a run of kRunQ samples
+__device__ __forceinline__ float density_run(const float4* __restrict__ tile, float xq, float xl, float cf) {
+  float run = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < kRunQ / 4; ++k) {
+    const float4 v = tile[k];
+    const float xs[4] = {v.x, v.y, v.z, v.w};
+    float e[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float d = (xq - xs[u]) + xl;
+      e[u] = d * d * cf;
+    }
+    exp2_group(e);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) run += e[u];
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return run;
+}
+
 // grid (query blocks, pieces); part[q * pieces + piece].  Bound: vector
 // issue, 8.1 cycles for the exponential and 2.4 for each of five plain
 // instructions a term; the four samples of an LDS read issue their
@@ -83,26 +104,51 @@ __global__ __launch_bounds__(kThreads) void k_density_f32(const ColDesc* __restr
     for (int k = threadIdx.x; k < kBJ / 4; k += kThreads) tile[k] = reinterpret_cast<const float4*>(x + t0)[k];
     __syncthreads();
     for (int r0 = 0; r0 < kBJ; r0 += kRunQ) {
-      float run = 0.f;
-#pragma unroll 4
-      for (int k = 0; k < kRunQ / 4; ++k) {
-        const float4 v = tile[(r0 >> 2) + k];
-        const float xs[4] = {v.x, v.y, v.z, v.w};
-        float e[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float d = (xq - xs[u]) + xl;
-          e[u] = d * d * cf;
-        }
-        exp2_group(e);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) run += e[u];
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      fold(a, comp, run);
+      fold(a, comp, density_run(tile + (r0 >> 2), xq, xl, cf));
     }
   }
   if (qi < m) part[(int64_t)qi * pieces + blockIdx.y] = (double)a - (double)comp;
+}
+
+// The same piece of the column for 64 query points, by the sixteen waves of a
+// block: a run a wave and step, whose sums one wave folds in ascending order,
+// so that a point's sum is the same as from k_density_f32 bit for bit.  For
+// calls of few points, where a wave that is alone on its SIMD issues an
+// instruction every 5-8 cycles and walks 4096 samples by itself: a call of 64
+// points over n = 1e5 samples 204 -> 80 us, 512 over 1e6 209 -> 148 us.
+constexpr int kWideWaves = 16;
+__global__ __launch_bounds__(64 * kWideWaves) void k_density_wide_f32(const ColDesc* __restrict__ col,
+                                                                      const double* __restrict__ q, int m, double h,
+                                                                      int piece_len, int pieces,
+                                                                      double* __restrict__ part) {
+  constexpr int kTile = kRunQ * kWideWaves;
+  const ColDesc c = *col;
+  const float* x = c.x32;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qi = blockIdx.x * 64 + lane;
+  const double xq64 = qi < m ? q[qi] - c.st->shift : 0.0;
+  const float xq = (float)xq64;
+  const float xl = (float)(xq64 - (double)xq);
+  const float cf = (float)(-kLog2E / (2.0 * h * h));
+  const int n_pad = (c.n + kBJ - 1) / kBJ * kBJ;
+  const int j0 = blockIdx.y * piece_len;
+  const int j1 = min(j0 + piece_len, n_pad);
+  __shared__ float4 tile[kTile / 4];
+  __shared__ float sums[kWideWaves][64];
+  float a = 0.f, comp = 0.f;
+  for (int t0 = j0; t0 < j1; t0 += kTile) {
+    // every wave has swept the tile before (the second barrier below)
+    if (tid < min(kTile, j1 - t0) / 4) tile[tid] = reinterpret_cast<const float4*>(x + t0)[tid];
+    __syncthreads();  // the tile stands; wave 0 has folded the runs before
+    if (t0 + wave * kRunQ < j1) sums[wave][lane] = density_run(tile + wave * (kRunQ / 4), xq, xl, cf);
+    __syncthreads();
+    if (wave == 0) {
+      const int runs = min(kWideWaves, (j1 - t0) / kRunQ);
+      for (int r = 0; r < runs; ++r) fold(a, comp, sums[r][lane]);
+    }
+  }
+  if (wave == 0 && qi < m) part[(int64_t)qi * pieces + blockIdx.y] = (double)a - (double)comp;
 }
 
 __global__ __launch_bounds__(kThreads) void k_density_f64(const ColDesc* __restrict__ col,
@@ -301,12 +347,20 @@ __global__ __launch_bounds__(kThreads) void k_range_final(const ColDesc* __restr
   }
 }
 
-// pieces so that a launch has about 4096 blocks, each piece at least 4096 samples
-int pieces_for(int64_t n, int64_t other_blocks) {
+// pieces so that a launch has about 4096 blocks, each piece at least `least` samples
+int pieces_for(int64_t n, int64_t other_blocks, int64_t least = 4096) {
   const int64_t want = std::max<int64_t>(1, 4096 / std::max<int64_t>(1, other_blocks));
-  const int64_t most = std::max<int64_t>(1, n / 4096);
+  const int64_t most = std::max<int64_t>(1, n / least);
   return (int)std::min(want, most);
 }
+
+// 64-point blocks of sixteen waves below this many blocks of 256 points (twelve
+// a CU; the chip holds eight, and a last round that is partly empty costs more
+// the fewer and longer the blocks are).  n = 1e6, calls of 2000, 3000, 4096
+// points (1952, 2928, 3904 blocks of 256): 372, 522, 633 us in 256-point
+// blocks, 363, 497, 649 us in 64-point blocks; n = 4e5, 4096 points (1568):
+// 301 and 245 us.
+constexpr int kDensityWide = 3072;
 
 }  // namespace
 
@@ -339,7 +393,9 @@ kde_status kde_density(kde_ctx* c, kde_column x, double h, const double* points,
   const int n = (int)x.n;
   const int qblocks = (m + kde::kThreads - 1) / kde::kThreads;
   const int n_pad = (n + kde::kBJ - 1) / kde::kBJ * kde::kBJ;
-  int pieces = kde::pieces_for(n_pad, qblocks);
+  // the FP64 sums don't depend on the cut (beyond 1e-16); the compensated FP32
+  // sums do (up to 1e-8 in narrow estimates), and keep theirs
+  int pieces = kde::pieces_for(n_pad, qblocks, f64 ? kde::kBJ : 4096);
   int piece_len = (n_pad + pieces - 1) / pieces;
   piece_len = (piece_len + kde::kBJ - 1) / kde::kBJ * kde::kBJ;
   pieces = (n_pad + piece_len - 1) / piece_len;
@@ -353,6 +409,9 @@ kde_status kde_density(kde_ctx* c, kde_column x, double h, const double* points,
   const dim3 grid(qblocks, pieces);
   if (f64)
     kde::k_density_f64<<<grid, kde::kThreads, 0, c->stream>>>(dcol, dq, m, h, piece_len, pieces, dpart);
+  else if (qblocks * pieces < kde::kDensityWide)
+    kde::k_density_wide_f32<<<dim3((m + 63) / 64, pieces), 64 * kde::kWideWaves, 0, c->stream>>>(dcol, dq, m, h, piece_len,
+                                                                                               pieces, dpart);
   else
     kde::k_density_f32<<<grid, kde::kThreads, 0, c->stream>>>(dcol, dq, m, h, piece_len, pieces, dpart);
   kde::k_density_final<<<m, kde::kThreads, 0, c->stream>>>(dcol, dpart, pieces, h, dout);
