@@ -133,34 +133,37 @@ __device__ __forceinline__ void hz_run(const float (*tile)[kBJ], int jl, int jg,
   float r1[IB], r2[IB];
 #pragma unroll
   for (int w = 0; w < IB; ++w) r1[w] = r2[w] = 0.f;
-#pragma unroll 2
-  for (int q = 0; q < kMdRun; q += 4) {
-    float zj[D][4];
+  constexpr int J = 8 / IB;  // samples j a step: eight exponentials in a group
+#pragma unroll IB
+  for (int q = 0; q < kMdRun; q += J) {
+    float zj[D][J];
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      const float4 v = *reinterpret_cast<const float4*>(&tile[a][jl + q]);
-      zj[a][0] = v.x;
-      zj[a][1] = v.y;
-      zj[a][2] = v.z;
-      zj[a][3] = v.w;
-    }
-    float e[4 * IB];
+    for (int a = 0; a < D; ++a)
 #pragma unroll
-    for (int u = 0; u < 4 * IB; ++u) {
+      for (int u = 0; u < J; u += 4) {
+        const float4 v = *reinterpret_cast<const float4*>(&tile[a][jl + q + u]);
+        zj[a][u] = v.x;
+        zj[a][u + 1] = v.y;
+        zj[a][u + 2] = v.z;
+        zj[a][u + 3] = v.w;
+      }
+    float e[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
       float s = 0.f;
 #pragma unroll
       for (int a = 0; a < D; ++a) {
-        const float dd = zi[u >> 2][a] - zj[a][u & 3];
+        const float dd = zi[u / J][a] - zj[a][u % J];
         s = __builtin_fmaf(dd, dd, s);
       }
-      if (MASK) s = (jg + q + (u & 3) > i + 64 * (u >> 2)) ? s : __builtin_inff();
+      if (MASK) s = (jg + q + u % J > i + 64 * (u / J)) ? s : __builtin_inff();
       e[u] = -s;
     }
     exp2_group(e);
 #pragma unroll
-    for (int u = 0; u < 4 * IB; ++u) {
-      r1[u >> 2] += e[u];
-      r2[u >> 2] = __builtin_fmaf(e[u], e[u], r2[u >> 2]);
+    for (int u = 0; u < 8; ++u) {
+      r1[u / J] += e[u];
+      r2[u / J] = __builtin_fmaf(e[u], e[u], r2[u / J]);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -180,7 +183,9 @@ __device__ __forceinline__ void hz_run(const float (*tile)[kBJ], int jl, int jg,
 // of that time.  One matrix over n = 1e5, d = 2: sweep 1008 -> 812 us (25.6
 // cycles a pair; the parts add up to 22.5).  IB = 1 where the units would not
 // fill the chip with half the waves (n = 2500, d = 2: a call of 92 us against
-// 98).
+// 98), with eight samples j a step instead of four, so that a wave alone on its
+// SIMD has as many independent terms in flight (eight matrices, n = 5000: a
+// call of 252 us with four, 221 with eight).
 template <int D, int IB>
 __global__ __launch_bounds__(kThreads / IB) void k_HZ_units_f32(const float* __restrict__ z, int npad,
                                                                 const MdState* __restrict__ st,
