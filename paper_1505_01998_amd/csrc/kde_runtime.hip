@@ -705,10 +705,14 @@ int queue_blocks(kde_ctx* c, int hc, int tj) {
 }
 
 // The dense LSCV pass of `it` runs as one persistent launch (mixed form, the
-// vector-ALU sweep, option persistent, a variant the device can hold).
+// vector-ALU sweep, option persistent, a variant the device can hold) where
+// launches of a block per unit would have to be several, each with an end at
+// which the chip runs empty.
 bool lscv_queue_form(kde_ctx* c, const IterPlan& it) {
-  return c->prec != KDE_PREC_FP64 && !c->job_mfma && c->opt_persistent && !it.lscv_units.empty() &&
-         queue_blocks(c, c->job_hc, c->job_tj) > 0;
+  if (c->prec == KDE_PREC_FP64 || c->job_mfma || !c->opt_persistent || it.lscv_units.empty()) return false;
+  double evals = 0.0;
+  for (const UnitCost& u : it.lscv_cost) evals += u.evals;
+  return evals > c->opt_launch_evals && queue_blocks(c, c->job_hc, c->job_tj) > 0;
 }
 
 kde_status collect_ready_timing(kde_ctx* c) {
