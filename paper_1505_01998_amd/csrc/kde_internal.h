@@ -186,7 +186,7 @@ struct DevState {
   double h_plugin;
   double h_best, margin;
   double fp64_kappa;  // kappa threshold for the FP64 re-run (0 = never)
-  float psi_scale;  // FP32 1/g of the current psi pass (the scaled copy is x32 * psi_scale)
+  float psi_scale;  // FP32 1/g of the current psi pass (its samples are x32 * psi_scale)
   int psi_fast;     // the scaled copy's range keeps every Hermite value finite (no clamp needed)
   double cd[2];     // FP64 pair coefficients: 1/g^2, -1/(2 g^2)
   float xmin, xmax; // range of the FP32 working copy
@@ -199,7 +199,7 @@ struct DevState {
 struct ColDesc {
   const void* raw;      // input samples, float32 or float64
   float* x32;           // padded FP32 working copy [n + kPad]
-  float* y32;           // psi pass: the working copy times 1/g of the current stage [n + kPad] (may be null)
+  float* y32;           // psi pass of a large column: the working copy times 1/g of the stage [n + kPad] (may be null)
   double* x64;          // padded FP64 working copy [n + kPad] (may be null)
   double* stat;         // moment partials [kStatBlocks]
   float* stat_mm;       // minimum and maximum partials of the FP32 working copy [2][kStatBlocks]
@@ -248,13 +248,18 @@ struct RowDesc {
 
 // ---- launchers (kde_kernels.hip); all asynchronous on `s` ----
 // Column-level launches act on the columns cols[ids[0 .. n_ids)].
-void launch_stats(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int max_blocks);
-// Pilot bandwidth of the stage and, for the mixed form, the scaled copy
-// y32 = x32 / g of every active column.
-void launch_psi_begin(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int stage, int f64);
+// A step of the plug-in rule, by one thread of a column: 0, 1, 2: the pilot
+// bandwidth of that stage; kStepFinal: the bandwidth from psi_4; -1: none.
+constexpr int kStepFinal = 3;
+// Moments and normal-reference bandwidth, then the step `next` and, with
+// hc > 0, the bandwidth grid (launch_lscv_prep) of the same columns.
+void launch_stats(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int max_blocks, int next, int hc);
+void launch_plugin_step(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int step);
+// Mixed form, large columns: the scaled copy y32 = x32 / g of every active column.
+void launch_psi_scale(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids);
+// Sums of the units' partials, the stage's functional, then the step `next`.
 void launch_psi_finish(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int stage, int was_f64,
-                       int conditional);
-void launch_plugin_final(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids);
+                       int conditional, int next);
 void launch_lscv_prep(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int hc);
 void launch_lscv_finalize(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int f64);
 // Pair kernels act on units[u0 .. u0 + n_units).  wide: units of 64 samples i.

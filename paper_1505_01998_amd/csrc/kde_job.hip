@@ -220,12 +220,11 @@ kde_status kde_job_run(kde_job* j, double max_evals, int* done_out) {
   if (p.plugin && !j->plugin_done) {
     while (j->stage < 3) {
       const int s = j->stage;
-      if (j->psi_next == 0) it.ids_begin[s].push_back(0);
+      if (j->psi_next == 0) kde::begin_stage(p, 0, s, it);
       take(j->psi_u, j->psi_c, j->psi_next, left, first, it.psi_units[s], it.psi_cost[s], j->remaining);
       first = false;
       if (j->psi_next < j->psi_u.size()) break;
       it.ids_finish[s].push_back(0);
-      kde::psi_rows_of(p, d, it.psi_rows[s]);
       if (j->cond) kde::psi_units_of(p, 0, it.psi_cond_units[s], it.psi_cond_cost[s]);
       j->stage++;
       j->psi_next = 0;

@@ -262,40 +262,12 @@ __global__ __launch_bounds__(kThreads) void k_stats_dev(const ColDesc* __restric
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_stats_final(const ColDesc* __restrict__ cols,
-                                                          const int* __restrict__ ids) {
-  const ColDesc c = cols[ids[blockIdx.x]];
-  const int nblk = stat_blocks(c.n);
-  __shared__ double sh[kThreads];
-  __shared__ float shm[2 * kThreads];
-  double s = 0.0;
-  float lo = kInfF, hi = -kInfF;
-  for (int b = threadIdx.x; b < nblk; b += kThreads) {
-    s += c.stat[b];
-    lo = fminf(lo, c.stat_mm[b]);
-    hi = fmaxf(hi, c.stat_mm[kStatBlocks + b]);
-  }
-  s = block_sum(s, sh);
-  block_minmax(lo, hi, shm);
-  if (threadIdx.x == 0) {
-    DevState& d = *c.st;
-    d.xmin = lo;
-    d.xmax = hi;
-    const double n = d.n;
-    d.var = s / (n - 1.0);
-    d.sigma = sqrt(d.var);
-    // normal-reference rule: (4/3)^(1/5) sigma n^(-1/5)
-    d.h_rot = pow(4.0 / 3.0, 0.2) * pow(n, -0.2) * d.sigma;
-    if (d.status == kStOk && !(d.sigma > 0.0 && isfinite(d.sigma))) d.status = kStDegenerate;
-  }
-}
-
 // ------------------------------------------------------------------ plug-in scalar steps
-// One thread per column.  Stage s in {0, 1, 2} estimates psi_r, r = 8 - 2 s.
-__global__ void k_psi_begin(const ColDesc* __restrict__ cols, const int* __restrict__ ids, int n_ids, int stage) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_ids) return;
-  DevState& d = *cols[ids[k]].st;
+// Each by one thread of a column.  Stage s in {0, 1, 2} estimates psi_r,
+// r = 8 - 2 s.  A step that follows another one at once (the pass's lists name
+// the same columns) runs at the end of that one's kernel: small calls are
+// bound by the number of their launches, 2-4 us each.
+__device__ void psi_begin(DevState& d, int stage) {
   d.active = 0;
   d.need_f64 = 0;
   if (d.status != kStOk || d.pstatus != kStOk || d.stages == 0) return;
@@ -327,8 +299,32 @@ __global__ void k_psi_begin(const ColDesc* __restrict__ cols, const int* __restr
   d.cd[1] = -0.5 * ig2;
 }
 
-// Scaled copy of the mixed form's psi pass: y = x32 * (1/g) in FP32 (padding
-// stays +inf).  Grid (blocks, columns); inactive columns are skipped.
+__device__ void plugin_final(DevState& d) {
+  if (d.status != kStOk || d.pstatus != kStOk || d.stages == 0) return;
+  // h = [R(K) / (mu_2^2 psi_4 n)]^(1/5), R(K) = 1/(2 sqrt(pi))
+  const double rad = (0.5 / sqrt(kPi)) / (d.psi[2] * d.n);
+  if (!(rad > 0.0) || !isfinite(rad)) {
+    d.pstatus = kStDegenerate;
+    return;
+  }
+  d.h_plugin = pow(rad, 0.2);
+}
+
+__device__ __forceinline__ void plugin_step(DevState& d, int step) {
+  if (step == kStepFinal)
+    plugin_final(d);
+  else if (step >= 0)
+    psi_begin(d, step);
+}
+
+__global__ void k_plugin_step(const ColDesc* __restrict__ cols, const int* __restrict__ ids, int n_ids, int step) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n_ids) plugin_step(*cols[ids[k]].st, step);
+}
+
+// Scaled copy of a large column for the mixed form's psi pass: y = x32 * (1/g)
+// in FP32 (padding stays +inf).  Grid (blocks, columns); inactive columns are
+// skipped.  Small columns are scaled as their units load them.
 __global__ __launch_bounds__(kThreads) void k_psi_scale(const ColDesc* __restrict__ cols,
                                                         const int* __restrict__ ids) {
   const ColDesc c = cols[ids[blockIdx.y]];
@@ -339,44 +335,129 @@ __global__ __launch_bounds__(kThreads) void k_psi_scale(const ColDesc* __restric
     c.y32[i] = i < c.n ? c.x32[i] * s : kInfF;
 }
 
-// psi_sums[0] = sum_{i<j} He_r(u) e^{-u^2/2}, psi_sums[1] = sum of its
-// absolute value, u = (X_i - X_j)/g.  psi_r = [2 sum K^(r) + n K^(r)(0)] / (n^2 g^(r+1)).
-// conditional: this is the FP64 re-run of the mixed form; skip unless flagged.
-__global__ void k_psi_finish(const ColDesc* __restrict__ cols, const int* __restrict__ ids, int n_ids, int stage,
-                             int was_f64, int conditional) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_ids) return;
-  const ColDesc& c = cols[ids[k]];
+// Block per column: psi_sums[0] = sum_{i<j} He_r(u) e^{-u^2/2}, psi_sums[1] =
+// sum of its absolute value, u = (X_i - X_j)/g, from the units' partials in a
+// fixed order, then psi_r = [2 sum K^(r) + n K^(r)(0)] / (n^2 g^(r+1)).
+// conditional: this is the FP64 re-run of the mixed form; the stage stands
+// unless flagged.  next: the step that follows (-1: none).
+__global__ __launch_bounds__(kThreads) void k_psi_finish(const ColDesc* __restrict__ cols,
+                                                         const int* __restrict__ ids, int stage, int was_f64,
+                                                         int conditional, int next) {
+  const ColDesc& c = cols[ids[blockIdx.x]];
   DevState& d = *c.st;
-  const double* sums = c.psi_sums;
-  if (!d.active) return;
-  if (conditional && !d.need_f64) return;
-  const int r = 8 - 2 * stage;
-  const double inv_s2pi = 1.0 / sqrt(2.0 * kPi);
-  const double n = d.n, g = d.g[stage];
-  const double s = sums[0] * inv_s2pi, a = sums[1] * inv_s2pi;
-  d.psi[stage] = (2.0 * s + n * herm_at0(r) * inv_s2pi) / (n * n * pow(g, (double)(r + 1)));
-  d.kappa[stage] = (s != 0.0) ? a / fabs(s) : kInfD;
-  d.prec_used[stage] = was_f64 ? 1 : 0;
-  if (was_f64) {
-    d.need_f64 = 0;
-  } else {
-    d.need_f64 = (d.fp64_kappa > 0.0 && d.kappa[stage] > d.fp64_kappa) ? 1 : 0;
+  __shared__ double sh[2][kThreads];
+  const int t = threadIdx.x;
+  const bool todo = d.active && !(conditional && !d.need_f64);  // uniform over the block
+  __syncthreads();  // every wave has read the flags that thread 0 changes below
+  if (todo) {
+    const int m = c.n_items_psi;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 8
+    for (int k = t; k < m; k += kThreads) {
+      s0 += c.psi_part[k];
+      s1 += c.psi_part[m + k];
+    }
+    sh[0][t] = s0;
+    sh[1][t] = s1;
+    __syncthreads();
+    for (int s = kThreads / 2; s > 0; s >>= 1) {
+      if (t < s) {
+        sh[0][t] += sh[0][t + s];
+        sh[1][t] += sh[1][t + s];
+      }
+      __syncthreads();
+    }
+  }
+  if (t != 0) return;
+  if (todo) {
+    c.psi_sums[0] = sh[0][0];
+    c.psi_sums[1] = sh[1][0];
+    const int r = 8 - 2 * stage;
+    const double inv_s2pi = 1.0 / sqrt(2.0 * kPi);
+    const double n = d.n, g = d.g[stage];
+    const double s = sh[0][0] * inv_s2pi, a = sh[1][0] * inv_s2pi;
+    d.psi[stage] = (2.0 * s + n * herm_at0(r) * inv_s2pi) / (n * n * pow(g, (double)(r + 1)));
+    d.kappa[stage] = (s != 0.0) ? a / fabs(s) : kInfD;
+    d.prec_used[stage] = was_f64 ? 1 : 0;
+    if (was_f64) {
+      d.need_f64 = 0;
+    } else {
+      d.need_f64 = (d.fp64_kappa > 0.0 && d.kappa[stage] > d.fp64_kappa) ? 1 : 0;
+    }
+  }
+  plugin_step(d, next);
+}
+
+// By a block.  Grid point k of the column: explicit h_in[k], the
+// paper's default (linear over sigma [h0/4, 4 h0] = h_rot [1/4, 4]) or log-spaced
+// over h_rot [lo, hi].  c32 = -log2(e) / (4 h^2), so exp2(D^2 c32) =
+// exp(-D^2/(4 h^2)) and its square is exp(-D^2/(2 h^2)); c64 = -1/(4 h^2).
+// Entries past n_h up to the chunk multiple hold -1 (finite, unused).
+__device__ void lscv_prep(const ColDesc& c, double hr, int hc) {
+  const int m = c.n_chunks * hc;
+  for (int k = threadIdx.x; k < m; k += kThreads) {
+    const int o = k;
+    if (k < c.n_h) {
+      double h;
+      const double t = (c.n_h == 1) ? 0.0 : (double)k / (double)(c.n_h - 1);
+      if (c.grid_kind == kGridExplicit)
+        h = c.h_in[o];
+      else if (c.grid_kind == kGridPaper)
+        h = hr * 0.25 + (hr * 4.0 - hr * 0.25) * t;
+      else
+        h = hr * exp(log(c.grid_lo) + (log(c.grid_hi) - log(c.grid_lo)) * t);
+      c.h[o] = h;
+      const double q = 1.0 / (4.0 * h * h);
+      c.c32[o] = (float)(-kLog2E * q);
+      c.c64[o] = -q;
+    } else {
+      c.h[o] = 0.0;
+      c.c32[o] = -1.0f;
+      c.c64[o] = -1.0;
+    }
   }
 }
 
-__global__ void k_plugin_final(const ColDesc* __restrict__ cols, const int* __restrict__ ids, int n_ids) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_ids) return;
-  DevState& d = *cols[ids[k]].st;
-  if (d.status != kStOk || d.pstatus != kStOk || d.stages == 0) return;
-  // h = [R(K) / (mu_2^2 psi_4 n)]^(1/5), R(K) = 1/(2 sqrt(pi))
-  const double rad = (0.5 / sqrt(kPi)) / (d.psi[2] * d.n);
-  if (!(rad > 0.0) || !isfinite(rad)) {
-    d.pstatus = kStDegenerate;
-    return;
+__global__ __launch_bounds__(kThreads) void k_lscv_prep(const ColDesc* __restrict__ cols,
+                                                        const int* __restrict__ ids, int hc) {
+  const ColDesc c = cols[ids[blockIdx.x]];
+  if (c.n_h > 0) lscv_prep(c, c.st->h_rot, hc);
+}
+
+// Spread and normal-reference bandwidth; then, where they follow at once, the
+// first plug-in step (next) and the bandwidth grid (hc > 0).
+__global__ __launch_bounds__(kThreads) void k_stats_final(const ColDesc* __restrict__ cols,
+                                                          const int* __restrict__ ids, int next, int hc) {
+  const ColDesc c = cols[ids[blockIdx.x]];
+  const int nblk = stat_blocks(c.n);
+  __shared__ double sh[kThreads];
+  __shared__ float shm[2 * kThreads];
+  double s = 0.0;
+  float lo = kInfF, hi = -kInfF;
+  for (int b = threadIdx.x; b < nblk; b += kThreads) {
+    s += c.stat[b];
+    lo = fminf(lo, c.stat_mm[b]);
+    hi = fmaxf(hi, c.stat_mm[kStatBlocks + b]);
   }
-  d.h_plugin = pow(rad, 0.2);
+  s = block_sum(s, sh);
+  block_minmax(lo, hi, shm);
+  if (threadIdx.x == 0) {
+    DevState& d = *c.st;
+    d.xmin = lo;
+    d.xmax = hi;
+    const double n = d.n;
+    d.var = s / (n - 1.0);
+    d.sigma = sqrt(d.var);
+    // normal-reference rule: (4/3)^(1/5) sigma n^(-1/5)
+    d.h_rot = pow(4.0 / 3.0, 0.2) * pow(n, -0.2) * d.sigma;
+    if (d.status == kStOk && !(d.sigma > 0.0 && isfinite(d.sigma))) d.status = kStDegenerate;
+    sh[0] = d.h_rot;
+    plugin_step(d, next);
+  }
+  if (hc > 0 && c.n_h > 0) {
+    __syncthreads();
+    lscv_prep(c, sh[0], hc);
+  }
 }
 
 // Where a unit's sweep ends: its j-range, cut to the runs of kRun that hold a
@@ -509,7 +590,8 @@ __global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))
   const Unit u = units[u0 + blockIdx.x];
   const ColDesc c = cols[u.col];
   if (!c.st->active) return;
-  const float* y = c.y32;
+  const float* x = c.x32;
+  const float scale = c.st->psi_scale;
   const int n = c.n;
   const bool fast = c.st->psi_fast != 0;
   __shared__ __attribute__((aligned(16))) float tile[2][kPsiTile];
@@ -518,15 +600,23 @@ __global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i0 = u.row * 64;
   const int i = i0 + lane;
-  const float yi = (i < n) ? y[i] : 0.f;
+  // rounded products, as in the scaled copy (padding: +inf, or NaN times a
+  // scale of 0, which the clamp of padded tiles takes as far away)
+  const auto y = [&](int j) {
+#pragma clang fp contract(off)
+    float v = x[j] * scale;
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  const float yi = (i < n) ? y(i) : 0.f;
   const int j_begin = max(u.j_begin, i0), j_end = unit_end(u, n);
   float acc = 0.f, comp = 0.f;  // waves 0 and 1: the lane's folded sums
-  if (j_begin + tid < j_end) tile[0][tid] = y[j_begin + tid];
+  if (j_begin + tid < j_end) tile[0][tid] = y(j_begin + tid);
   __syncthreads();
   for (int t0 = j_begin, b = 0; t0 < j_end; t0 += kPsiTile, b ^= 1) {
     const int jn = t0 + kPsiTile + tid;
     float next = 0.f;
-    if (jn < j_end) next = y[jn];
+    if (jn < j_end) next = y(jn);
     const int js = t0 + wave * kRun;
     if (js < j_end) {
       const float4* run = reinterpret_cast<const float4*>(&tile[b][wave * kRun]);
@@ -671,40 +761,6 @@ __global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))
 }
 
 // ------------------------------------------------------------------ LSCV kernels
-// Block per column.  Grid point k of the column: explicit h_in[k], the
-// paper's default (linear over sigma [h0/4, 4 h0] = h_rot [1/4, 4]) or log-spaced
-// over h_rot [lo, hi].  c32 = -log2(e) / (4 h^2), so exp2(D^2 c32) =
-// exp(-D^2/(4 h^2)) and its square is exp(-D^2/(2 h^2)); c64 = -1/(4 h^2).
-// Entries past n_h up to the chunk multiple hold -1 (finite, unused).
-__global__ __launch_bounds__(kThreads) void k_lscv_prep(const ColDesc* __restrict__ cols,
-                                                        const int* __restrict__ ids, int hc) {
-  const ColDesc c = cols[ids[blockIdx.x]];
-  if (c.n_h <= 0) return;
-  const double hr = c.st->h_rot;
-  const int m = c.n_chunks * hc;
-  for (int k = threadIdx.x; k < m; k += kThreads) {
-    const int o = k;
-    if (k < c.n_h) {
-      double h;
-      const double t = (c.n_h == 1) ? 0.0 : (double)k / (double)(c.n_h - 1);
-      if (c.grid_kind == kGridExplicit)
-        h = c.h_in[o];
-      else if (c.grid_kind == kGridPaper)
-        h = hr * 0.25 + (hr * 4.0 - hr * 0.25) * t;
-      else
-        h = hr * exp(log(c.grid_lo) + (log(c.grid_hi) - log(c.grid_lo)) * t);
-      c.h[o] = h;
-      const double q = 1.0 / (4.0 * h * h);
-      c.c32[o] = (float)(-kLog2E * q);
-      c.c64[o] = -q;
-    } else {
-      c.h[o] = 0.0;
-      c.c32[o] = -1.0f;
-      c.c64[o] = -1.0;
-    }
-  }
-}
-
 // Four consecutive j of a run (one float4 of the LDS tile) against the
 // lane's sample, for the HC bandwidths.  FIRST: the run's first pair starts
 // the plain sums (S1 = e, S2 = e e instead of adding them to zero: the same
@@ -1363,28 +1419,26 @@ __global__ __launch_bounds__(kThreads) void k_reduce_rows(const RowDesc* __restr
 // ------------------------------------------------------------------ launchers
 static inline int id_blocks(int n_ids) { return (n_ids + kThreads - 1) / kThreads; }
 
-void launch_stats(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int max_blocks) {
+void launch_stats(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int max_blocks, int next, int hc) {
   if (n_ids <= 0) return;
   const dim3 grid2(max_blocks, n_ids);
   k_stats_sum<<<grid2, kThreads, 0, s>>>(cols, ids);
   k_stats_mean<<<n_ids, kThreads, 0, s>>>(cols, ids);
   k_stats_dev<<<grid2, kThreads, 0, s>>>(cols, ids);
-  k_stats_final<<<n_ids, kThreads, 0, s>>>(cols, ids);
+  k_stats_final<<<n_ids, kThreads, 0, s>>>(cols, ids, next, hc);
 }
 
-void launch_psi_begin(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int stage, int f64) {
-  if (n_ids <= 0) return;
-  k_psi_begin<<<id_blocks(n_ids), kThreads, 0, s>>>(cols, ids, n_ids, stage);
-  if (!f64) k_psi_scale<<<dim3(128, n_ids), kThreads, 0, s>>>(cols, ids);
+void launch_plugin_step(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int step) {
+  if (n_ids > 0) k_plugin_step<<<id_blocks(n_ids), kThreads, 0, s>>>(cols, ids, n_ids, step);
+}
+
+void launch_psi_scale(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids) {
+  if (n_ids > 0) k_psi_scale<<<dim3(128, n_ids), kThreads, 0, s>>>(cols, ids);
 }
 
 void launch_psi_finish(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int stage, int was_f64,
-                       int conditional) {
-  if (n_ids > 0) k_psi_finish<<<id_blocks(n_ids), kThreads, 0, s>>>(cols, ids, n_ids, stage, was_f64, conditional);
-}
-
-void launch_plugin_final(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids) {
-  if (n_ids > 0) k_plugin_final<<<id_blocks(n_ids), kThreads, 0, s>>>(cols, ids, n_ids);
+                       int conditional, int next) {
+  if (n_ids > 0) k_psi_finish<<<n_ids, kThreads, 0, s>>>(cols, ids, stage, was_f64, conditional, next);
 }
 
 void launch_lscv_prep(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int hc) {

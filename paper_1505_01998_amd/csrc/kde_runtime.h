@@ -86,9 +86,9 @@ struct IterPlan {
   std::vector<ColDesc> cols;
   std::vector<int> ids_stats;
   std::vector<int> ids_begin[3], ids_finish[3];
+  std::vector<int> ids_scale[3];  // of ids_begin, the columns whose units read the scaled copy (mixed form, rows of 256)
   std::vector<Unit> psi_units[3];
   std::vector<UnitCost> psi_cost[3];
-  std::vector<RowDesc> psi_rows[3];
   // Columns added whole (add_full_column) run the same units in every stage
   // and in its FP64 re-run: one list, psi_units[1], serves them all.  A column
   // of two stages takes no part in stage 0; once one is added stage 0 has a
@@ -125,7 +125,7 @@ struct PassLayout {
   size_t sort_tmp = 0;                            // temporary bytes of the largest sort
   size_t o_ctr = 0;                               // work counters of the persistent launches (ints)
   size_t o_lg = 0;                                // group offsets of the persistent dense LSCV pass
-  size_t o_begin[3] = {0, 0, 0}, o_finish[3] = {0, 0, 0}, o_psu[3] = {0, 0, 0}, o_pr[3] = {0, 0, 0},
+  size_t o_begin[3] = {0, 0, 0}, o_finish[3] = {0, 0, 0}, o_psu[3] = {0, 0, 0}, o_scale[3] = {0, 0, 0},
          o_pc[3] = {0, 0, 0};
 };
 
@@ -337,7 +337,7 @@ void add_prune_setup(const ColPlan& p, const ColDesc& d, int id, int extra_id, I
 // Pieces used by the server to schedule a column's work over several passes.
 void psi_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost);
 void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost);
-void psi_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows);
+void begin_stage(const ColPlan& p, int id, int stage, IterPlan& it);
 void lscv_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows);
 void init_state(const ColPlan& p, double fp64_kappa, DevState& h);
 // Resets r (keeping its g/gscale pointers): h's NaN, k_lscv -1, status st.

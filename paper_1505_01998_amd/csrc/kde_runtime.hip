@@ -72,7 +72,7 @@ void IterPlan::clear() {
     ids_finish[s].clear();
     psi_units[s].clear();
     psi_cost[s].clear();
-    psi_rows[s].clear();
+    ids_scale[s].clear();
     psi_cond_units[s].clear();
     psi_cond_cost[s].clear();
   }
@@ -411,9 +411,9 @@ void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<U
     }
 }
 
-void psi_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows) {
-  const int m = d.n_items_psi;
-  for (int w = 0; w < 2; ++w) rows.push_back(RowDesc{d.psi_part + (size_t)w * m, d.psi_sums + w, m, 0});
+void begin_stage(const ColPlan& p, int id, int stage, IterPlan& it) {
+  it.ids_begin[stage].push_back(id);
+  if (p.off_y32 && p.psi_groups == 1) it.ids_scale[stage].push_back(id);
 }
 
 void lscv_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows) {
@@ -458,8 +458,7 @@ void add_full_column(const kde_ctx* c, const ColPlan& p, const ColDesc& d, int i
   it.max_stat_blocks = std::max(it.max_stat_blocks, std::min(kStatBlocks, (p.n + 2047) / 2048));
   if (p.plugin) {
     for (int s = (p.stages == 3 ? 0 : 1); s < 3; ++s) {
-      it.ids_begin[s].push_back(id);
-      psi_rows_of(p, d, it.psi_rows[s]);
+      begin_stage(p, id, s, it);
       it.ids_finish[s].push_back(id);
     }
     it.psi_shared = true;
@@ -763,7 +762,7 @@ kde_status pack_pass(kde_ctx* c, IterPlan& it, PassLayout& L) {
     L.o_begin[q] = b.add(it.ids_begin[q].data(), vbytes(it.ids_begin[q]));
     L.o_finish[q] = b.add(it.ids_finish[q].data(), vbytes(it.ids_finish[q]));
     if (it.psi_list(q) == q) L.o_psu[q] = b.add(it.psi_units[q].data(), vbytes(it.psi_units[q]));
-    L.o_pr[q] = b.add(it.psi_rows[q].data(), vbytes(it.psi_rows[q]));
+    L.o_scale[q] = b.add(it.ids_scale[q].data(), vbytes(it.ids_scale[q]));
     if (!it.psi_shared) L.o_pc[q] = b.add(it.psi_cond_units[q].data(), vbytes(it.psi_cond_units[q]));
   }
   if (it.psi_shared)
@@ -814,13 +813,28 @@ kde_status launch_pass(kde_ctx* c, const IterPlan& it, const PassLayout& L) {
   const ColDesc* cols = (const ColDesc*)(d + L.o_cols);
   auto ids = [&](size_t o) { return (const int*)(d + o); };
   hipStream_t st = c->stream;
+  const int hc = all64 ? 8 : c->job_hc;
+  // What follows the moments, and what follows stage q: the step that acts on
+  // the same columns next, if the lists agree (a synchronous call; a batch or
+  // an iteration of a server may mix columns of two and three stages, and
+  // columns at different stages), else -1: its own launch.
+  const auto step_after = [&](int q, const std::vector<int>& done) {
+    for (int s = q + 1; s < 3; ++s)
+      if (!it.ids_begin[s].empty()) return it.ids_begin[s] == done ? s : -1;
+    return !it.ids_plugin_final.empty() && it.ids_plugin_final == done ? kStepFinal : -1;
+  };
   // moments
-  kde::launch_stats(st, cols, ids(L.o_stats), (int)it.ids_stats.size(), it.max_stat_blocks);
+  const bool prep_follows = it.ids_lscv_prep == it.ids_stats;
+  int step = step_after(-1, it.ids_stats);
+  kde::launch_stats(st, cols, ids(L.o_stats), (int)it.ids_stats.size(), it.max_stat_blocks, step,
+                    prep_follows ? hc : 0);
   // plug-in stages
   for (int q = 0; q < 3; ++q) {
     if (it.ids_begin[q].empty() && it.psi_units[q].empty() && it.ids_finish[q].empty()) continue;
     const int r = 8 - 2 * q;
-    kde::launch_psi_begin(st, cols, ids(L.o_begin[q]), (int)it.ids_begin[q].size(), q, all64 ? 1 : 0);
+    if (step != q) kde::launch_plugin_step(st, cols, ids(L.o_begin[q]), (int)it.ids_begin[q].size(), q);
+    kde::launch_psi_scale(st, cols, ids(L.o_scale[q]), (int)it.ids_scale[q].size());
+    step = step_after(q, it.ids_finish[q]);
     const Unit* pu = (const Unit*)(d + L.o_psu[q]);
     const std::vector<UnitCost>& cost = it.psi_cost[it.psi_list(q)];
     const int narrow = it.psi_narrow[it.psi_list(q)];
@@ -837,11 +851,11 @@ kde_status launch_pass(kde_ctx* c, const IterPlan& it, const PassLayout& L) {
           wide ? narrow : 0, wide ? -1 : narrow);
       if (s) return s;
     }
-    kde::launch_reduce_rows(st, (const RowDesc*)(d + L.o_pr[q]), (int)it.psi_rows[q].size());
-    kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, all64 ? 1 : 0, 0);
     const std::vector<UnitCost>& cond_cost = it.psi_shared ? it.psi_cost[it.psi_list(q)] : it.psi_cond_cost[q];
-    const bool cond = it.psi_shared ? c->opt_fp64_kappa > 0.0 : !cond_cost.empty();
-    if (!all64 && cond && !cond_cost.empty()) {
+    const bool cond = !all64 && !cond_cost.empty() && (!it.psi_shared || c->opt_fp64_kappa > 0.0);
+    kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, all64 ? 1 : 0, 0,
+                           cond ? -1 : step);
+    if (cond) {
       // FP64 re-run of the columns whose stage is badly conditioned; blocks of
       // other columns exit at once, so these launches are not timed.
       const Unit* pc = (const Unit*)(d + L.o_pc[q]);
@@ -856,14 +870,13 @@ kde_status launch_pass(kde_ctx* c, const IterPlan& it, const PassLayout& L) {
             wide ? cond_narrow : 0, wide ? -1 : cond_narrow);
         if (s) return s;
       }
-      kde::launch_reduce_rows(st, (const RowDesc*)(d + L.o_pr[q]), (int)it.psi_rows[q].size());
-      kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, 1, 1);
+      kde::launch_psi_finish(st, cols, ids(L.o_finish[q]), (int)it.ids_finish[q].size(), q, 1, 1, step);
     }
   }
-  kde::launch_plugin_final(st, cols, ids(L.o_pf), (int)it.ids_plugin_final.size());
+  if (step != kStepFinal)
+    kde::launch_plugin_step(st, cols, ids(L.o_pf), (int)it.ids_plugin_final.size(), kStepFinal);
   // LSCV
-  const int hc = all64 ? 8 : c->job_hc;
-  kde::launch_lscv_prep(st, cols, ids(L.o_lp), (int)it.ids_lscv_prep.size(), hc);
+  if (!prep_follows) kde::launch_lscv_prep(st, cols, ids(L.o_lp), (int)it.ids_lscv_prep.size(), hc);
   // tile pruning: sort, near-tile lower bounds and cut distances of the
   // columns whose LSCV work starts in this pass, then the pruned units (a
   // served column's pruned units may span several passes)

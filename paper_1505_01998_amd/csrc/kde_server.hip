@@ -341,12 +341,11 @@ void Server::loop() {
       if (p.plugin && !r->plugin_done) {
         while (r->stage < 3) {
           const int s = r->stage;
-          if (r->psi_next == 0) it.ids_begin[s].push_back(r->slot);
+          if (r->psi_next == 0) begin_stage(p, r->slot, s, it);
           take_units(r->psi_u, r->psi_c, r->psi_next, left, first, it.psi_units[s], it.psi_cost[s], r->remaining);
           first = false;
           if (r->psi_next < r->psi_u.size()) break;
           it.ids_finish[s].push_back(r->slot);
-          psi_rows_of(p, d, it.psi_rows[s]);
           if (cond) psi_units_of(p, r->slot, it.psi_cond_units[s], it.psi_cond_cost[s]);
           r->stage++;
           r->psi_next = 0;
