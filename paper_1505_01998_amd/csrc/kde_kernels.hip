@@ -170,16 +170,15 @@ __device__ __forceinline__ double load_raw(const ColDesc& c, int i) {
 
 __device__ __forceinline__ int stat_blocks(int n) { return min(kStatBlocks, (n + 2047) / 2048); }
 
-// Pass 1: per-block FP64 sum of the samples and count of non-finite values.
-// Grid (max blocks, columns).
-__global__ __launch_bounds__(kThreads) void k_stats_sum(const ColDesc* __restrict__ cols, const int* __restrict__ ids) {
-  const ColDesc c = cols[ids[blockIdx.y]];
+// Pass 1: per-block FP64 sum of the samples and count of non-finite values;
+// block blk of the column's stat_blocks.
+__device__ void stats_sum(const ColDesc& c, int blk) {
   const int nblk = stat_blocks(c.n);
-  if ((int)blockIdx.x >= nblk) return;
+  if (blk >= nblk) return;
   __shared__ double sh[kThreads];
   __shared__ int nf_sh;
   const int chunk = (c.n + nblk - 1) / nblk;
-  const int b0 = blockIdx.x * chunk;
+  const int b0 = blk * chunk;
   const int b1 = min(c.n, b0 + chunk);
   if (threadIdx.x == 0) nf_sh = 0;
   __syncthreads();
@@ -192,15 +191,13 @@ __global__ __launch_bounds__(kThreads) void k_stats_sum(const ColDesc* __restric
   if (nf) atomicAdd(&nf_sh, nf);
   s = block_sum(s, sh);
   if (threadIdx.x == 0) {
-    c.stat[blockIdx.x] = s;
-    c.stat_nf[blockIdx.x] = nf_sh;
+    c.stat[blk] = s;
+    c.stat_nf[blk] = nf_sh;
   }
 }
 
-// Mean of each column (block per column); float64 columns are shifted by it.
-__global__ __launch_bounds__(kThreads) void k_stats_mean(const ColDesc* __restrict__ cols,
-                                                         const int* __restrict__ ids) {
-  const ColDesc c = cols[ids[blockIdx.x]];
+// Mean of a column (by one block); float64 columns are shifted by it.
+__device__ void stats_mean(const ColDesc& c) {
   const int nblk = stat_blocks(c.n);
   __shared__ double sh[kThreads];
   __shared__ int nf_sh;
@@ -225,16 +222,15 @@ __global__ __launch_bounds__(kThreads) void k_stats_mean(const ColDesc* __restri
 
 // Pass 2: per-block sum of squared deviations; writes the padded FP32 (and
 // FP64) working copies of the column.
-__global__ __launch_bounds__(kThreads) void k_stats_dev(const ColDesc* __restrict__ cols, const int* __restrict__ ids) {
-  const ColDesc c = cols[ids[blockIdx.y]];
+__device__ void stats_dev(const ColDesc& c, int blk) {
   const int nblk = stat_blocks(c.n);
-  if ((int)blockIdx.x >= nblk) return;
+  if (blk >= nblk) return;
   __shared__ double sh[kThreads];
   const double mean = c.st->mean, shift = c.st->shift;
   float* y32 = c.x32;
   double* y64 = c.x64;
   const int chunk = (c.n + nblk - 1) / nblk;
-  const int b0 = blockIdx.x * chunk;
+  const int b0 = blk * chunk;
   const int b1 = min(c.n, b0 + chunk);
   __shared__ float shm[2 * kThreads];
   double s = 0.0;
@@ -249,16 +245,16 @@ __global__ __launch_bounds__(kThreads) void k_stats_dev(const ColDesc* __restric
     hi = fmaxf(hi, w);
     if (y64) y64[i] = v;
   }
-  for (int i = c.n + blockIdx.x * kThreads + threadIdx.x; i < c.n + kPad; i += nblk * kThreads) {
+  for (int i = c.n + blk * kThreads + threadIdx.x; i < c.n + kPad; i += nblk * kThreads) {
     y32[i] = kInfF;
     if (y64) y64[i] = kInfD;
   }
   s = block_sum(s, sh);
   block_minmax(lo, hi, shm);
   if (threadIdx.x == 0) {
-    c.stat[blockIdx.x] = s;
-    c.stat_mm[blockIdx.x] = lo;
-    c.stat_mm[kStatBlocks + blockIdx.x] = hi;
+    c.stat[blk] = s;
+    c.stat_mm[blk] = lo;
+    c.stat_mm[kStatBlocks + blk] = hi;
   }
 }
 
@@ -426,9 +422,7 @@ __global__ __launch_bounds__(kThreads) void k_lscv_prep(const ColDesc* __restric
 
 // Spread and normal-reference bandwidth; then, where they follow at once, the
 // first plug-in step (next) and the bandwidth grid (hc > 0).
-__global__ __launch_bounds__(kThreads) void k_stats_final(const ColDesc* __restrict__ cols,
-                                                          const int* __restrict__ ids, int next, int hc) {
-  const ColDesc c = cols[ids[blockIdx.x]];
+__device__ void stats_final(const ColDesc& c, int next, int hc) {
   const int nblk = stat_blocks(c.n);
   __shared__ double sh[kThreads];
   __shared__ float shm[2 * kThreads];
@@ -458,6 +452,36 @@ __global__ __launch_bounds__(kThreads) void k_stats_final(const ColDesc* __restr
     __syncthreads();
     lscv_prep(c, sh[0], hc);
   }
+}
+
+// Grids (max blocks, columns) for the passes over the samples, (columns) else.
+__global__ __launch_bounds__(kThreads) void k_stats_sum(const ColDesc* __restrict__ cols, const int* __restrict__ ids) {
+  stats_sum(cols[ids[blockIdx.y]], blockIdx.x);
+}
+__global__ __launch_bounds__(kThreads) void k_stats_mean(const ColDesc* __restrict__ cols,
+                                                         const int* __restrict__ ids) {
+  stats_mean(cols[ids[blockIdx.x]]);
+}
+__global__ __launch_bounds__(kThreads) void k_stats_dev(const ColDesc* __restrict__ cols, const int* __restrict__ ids) {
+  stats_dev(cols[ids[blockIdx.y]], blockIdx.x);
+}
+__global__ __launch_bounds__(kThreads) void k_stats_final(const ColDesc* __restrict__ cols,
+                                                          const int* __restrict__ ids, int next, int hc) {
+  stats_final(cols[ids[blockIdx.x]], next, hc);
+}
+
+// Columns of one statistics block each (n <= 2048): the four passes by that
+// block, in one launch.  A call of 1000 samples 138 -> 132 us.
+__global__ __launch_bounds__(kThreads) void k_stats_one(const ColDesc* __restrict__ cols, const int* __restrict__ ids,
+                                                        int next, int hc) {
+  const ColDesc c = cols[ids[blockIdx.x]];
+  stats_sum(c, 0);
+  __syncthreads();
+  stats_mean(c);
+  __syncthreads();
+  stats_dev(c, 0);
+  __syncthreads();
+  stats_final(c, next, hc);
 }
 
 // Where a unit's sweep ends: its j-range, cut to the runs of kRun that hold a
@@ -1421,6 +1445,10 @@ static inline int id_blocks(int n_ids) { return (n_ids + kThreads - 1) / kThread
 
 void launch_stats(hipStream_t s, const ColDesc* cols, const int* ids, int n_ids, int max_blocks, int next, int hc) {
   if (n_ids <= 0) return;
+  if (max_blocks == 1) {
+    k_stats_one<<<n_ids, kThreads, 0, s>>>(cols, ids, next, hc);
+    return;
+  }
   const dim3 grid2(max_blocks, n_ids);
   k_stats_sum<<<grid2, kThreads, 0, s>>>(cols, ids);
   k_stats_mean<<<n_ids, kThreads, 0, s>>>(cols, ids);

@@ -46,3 +46,23 @@ def test_steps_of_mixed_batches_are_those_of_single_columns(precision, kappa):
         if r.methods & kde.KDE_METHOD_LSCV:
             assert a.k_lscv == b.k_lscv
             assert np.all(np.abs(a.g - b.g) <= 2.0**-38 * a.gscale)
+
+
+@pytest.mark.parametrize("n", [2, 255, 257, 2047, 2048])
+def test_moments_of_small_columns_do_not_depend_on_the_batch(n):
+    """One launch where every column of a call has at most 2048 samples, four
+    beside a longer one: the same sums, bit for bit; a column that holds a
+    non-finite value is refused by both."""
+    import paper_1505_01998_amd as kde
+
+    x, bad = workloads.draw("lognormal", n, 90 + n, np.float64), np.arange(n, dtype=np.float64)
+    bad[n // 2] = np.inf
+    rot = [kde.Request(v, kde.KDE_METHOD_ROT, 3, ("paper", 8)) for v in (x, bad)]
+    long = kde.Request(workloads.draw("gamma", 5000, 91, np.float32), kde.KDE_METHOD_ROT, 3, ("paper", 8))
+    with kde.Context(0) as c:
+        alone, beside = c.batch(rot), c.batch(rot + [long])
+    assert alone[0].status == beside[0].status == kde.KDE_OK
+    assert alone[0].sigma == beside[0].sigma and alone[0].h_rot == beside[0].h_rot
+    want = float(np.std(x, ddof=1))
+    assert abs(alone[0].sigma - want) <= (n + 10) * 2.0**-53 * want
+    assert alone[1].status == beside[1].status == kde.KDE_E_INVAL
