@@ -72,9 +72,9 @@ TRAFFIC_SOURCES = ("kde_internal.h", "kde_kernels.hip", "kde_runtime.hip")
 MEASURED_TRAFFIC = {
     "workload": "lognormal-1m",
     "kernel": "k_lscv_units_f32_queue<16, 512>",
-    "sources_sha256": "331fd9f42e6a0e5f0ee7c45868e630c3797f1e1b5cea1f62cb8610dc8401afd6",
-    "fetch_bytes": 1.71920e+08,
-    "write_bytes": 1.14624e+09,
+    "sources_sha256": "529139faa4833f98f924deebe625f562781722827e441fb1f1a44c27581a39c8",
+    "fetch_bytes": 1.69077e+08,
+    "write_bytes": 1.13775e+09,
 }
 
 
@@ -241,9 +241,10 @@ def _apply_options(ctx, args):
         ctx.set_option("serve_iter_ms", args.iter_ms)
 
 
-def _lscv_kernel(ctx, args, n, n_h):
+def _lscv_kernel(ctx, args, n, n_h, evals=None):
     """Name of the LSCV kernel the runs used (the autotuner's cached choice for
-    the job's largest column when tuning is on)."""
+    the job's largest column when tuning is on); evals: of the whole dense pass
+    (of the one column if not given)."""
     if args.precision != "mixed":
         return "k_lscv_units_f64<8>"
     if args.prune > 0:
@@ -251,13 +252,16 @@ def _lscv_kernel(ctx, args, n, n_h):
         return f"k_lscv_units_prune<{hc}>"
     if args.autotune > 0:
         hc, tj = ctx.autotune(n, n_h)[0]
-        return f"k_lscv_units_f32_queue<{hc}, {tj}>"
-    if args.mfma > 0:
+    elif args.mfma > 0:
         return "k_lscv_units_mfma"
-    hc = args.hc if args.hc > 0 else 16
-    tj = args.tj if getattr(args, "tj", -1) > 0 else 512
-    # the dense pass runs as one persistent launch unless switched off
-    return f"k_lscv_units_f32<{hc}>" if getattr(args, "persistent", -1) == 0 else f"k_lscv_units_f32_queue<{hc}, {tj}>"
+    else:
+        hc = args.hc if args.hc > 0 else 16
+        tj = args.tj if getattr(args, "tj", -1) > 0 else 512
+    # a dense pass longer than one bounded launch (the default "launch_evals")
+    # runs as one persistent launch unless switched off
+    long = (0.5 * n * (n - 1.0) * n_h if evals is None else evals) > 4e12
+    return f"k_lscv_units_f32_queue<{hc}, {tj}>" if long and getattr(args, "persistent", -1) != 0 \
+        else f"k_lscv_units_f32<{hc}>"
 
 
 def batch_bench(args):
@@ -293,7 +297,7 @@ def batch_bench(args):
     torch.cuda.synchronize()
     t_plain = time.perf_counter() - t0
     log(f"plain per-column calls done in {t_plain:.1f} s")
-    kernel = _lscv_kernel(ctx, args, max(s.n for s in specs), n_h)
+    kernel = _lscv_kernel(ctx, args, max(s.n for s in specs), n_h, sum(0.5 * s.n * (s.n - 1.0) * n_h for s in specs))
     ctx.close()
     achieved = evals_k / (ms * 1e-3)
     return {
@@ -368,7 +372,7 @@ def lscv_H_bench(args):
                    "H": np.asarray(H).tolist()},
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "Teval/s",
                      "frac": achieved / peak, "traffic": None,
-                     "kernel": "k_HZ_units_f32<2>" if args.precision == "mixed" else "k_HZ_units_f64<2>",
+                     "kernel": "k_HZ_units_f32<2, 2>" if args.precision == "mixed" else "k_HZ_units_f64<2>",
                      "launches": launches, "avg_launch_ms": ms / max(launches, 1),
                      "evals_per_launch": evals_k / max(launches, 1)},
     }

@@ -171,9 +171,10 @@ kde_status kde_ctx_set_precision(kde_ctx* ctx, kde_prec prec);
  *                  a job.
  *   "persistent"   1 (default): the dense mixed-precision LSCV pass of a job
  *                  (synchronous call, batch, server iteration, job slice) is
- *                  one launch of about as many blocks as the device holds,
- *                  which take the pass's work units in order, largest first,
- *                  from a device counter; 0: launches of bounded work
+ *                  one launch: of a block per work unit where its evaluations
+ *                  stay within "launch_evals", else of about as many blocks
+ *                  as the device holds, which take the units in order, largest
+ *                  first, from device counters; 0: launches of bounded work
  *                  ("launch_evals").  Results are bitwise the same.
  *   "graph"        1: the kernel launches of a synchronous call or kde_batch
  *                  are captured into a HIP graph; a later call with the same
