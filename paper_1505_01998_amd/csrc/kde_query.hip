@@ -246,6 +246,14 @@ constexpr double kCutIn = 9.0, kCutOut = 12.0;
 // is, however small (what the cut leaves out is below 2e-33 n).
 constexpr double kFullBelow = 0x1p-50;
 
+// Lanes of a wave read from LDS what other lanes of it stored: the wave's LDS
+// operations execute in program order, and this keeps the compiler to that
+// order (no instruction).
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // grid (ranges, pieces): one range per block.  Each wave passes its samples
 // once: those inside are counted, those at an end queue up in LDS until 64 of
 // them fill the wave, which then evaluates them together.  FULL: every sample
@@ -305,9 +313,12 @@ __global__ __launch_bounds__(kThreads) void k_range_f64(const ColDesc* __restric
     if (at_end) queue[wave][queued + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = x;
     queued += __popcll(m);
+    wave_order();
     if (queued >= 64) {
       queued -= 64;
-      evaluate(queue[wave][queued + lane]);
+      const double xq = queue[wave][queued + lane];
+      wave_order();
+      evaluate(xq);
     }
   }
   if (!FULL) {
