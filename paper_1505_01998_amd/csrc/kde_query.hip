@@ -229,13 +229,16 @@ __device__ __forceinline__ double mills(double s) {
   return t * p;
 }
 
-// phi(z), and the tail beyond z on z's side of 0: Q(|z|) with the sign of z
-// (at |z| >= 40 both are exactly 0, infinite z included).
+// phi(z), and the tail beyond z on z's side of 0: Q(|z|), negative for z < 0
+// (at |z| >= 40 both are exactly 0, infinite z included).  A z of -0 counts as
+// 0, here and in evaluate's comparisons: an end of -0 at a sample of 0 gives
+// it, and so does a distance that underflows.
 __device__ __forceinline__ void normal_tail(double z, double& phi, double& q) {
 #pragma clang fp contract(off)  // equal z give equal phi: an empty range is exactly 0
   const double s = fmin(fabs(z), 40.0);
   phi = kInvSqrt2Pi * exp_cw(-0.5 * s * s);
-  q = copysign(phi * mills(s), z);
+  q = phi * mills(s);
+  if (z < 0.0) q = -q;
 }
 
 // Samples whose kernel a range [a, b] does not cut need no evaluation: with
