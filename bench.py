@@ -241,6 +241,10 @@ def _apply_options(ctx, args):
         ctx.set_option("serve_iter_ms", args.iter_ms)
 
 
+# the library's default "launch_evals" (the bench does not change it)
+LAUNCH_EVALS = 4e12
+
+
 def _lscv_kernel(ctx, args, n, n_h, evals=None):
     """Name of the LSCV kernel the runs used (the autotuner's cached choice for
     the job's largest column when tuning is on); evals: of the whole dense pass
@@ -250,16 +254,15 @@ def _lscv_kernel(ctx, args, n, n_h, evals=None):
     if args.prune > 0:
         hc = ctx.autotune(n, n_h)[0][0] if args.autotune > 0 else (args.hc if args.hc > 0 else 16)
         return f"k_lscv_units_prune<{hc}>"
-    if args.autotune > 0:
+    # a dense pass longer than one bounded launch runs as one persistent launch
+    # unless switched off; only such passes take the autotuner's variant
+    long = (0.5 * n * (n - 1.0) * n_h if evals is None else evals) > LAUNCH_EVALS
+    hc = args.hc if args.hc > 0 else 16
+    tj = args.tj if getattr(args, "tj", -1) > 0 else 512
+    if args.autotune > 0 and long:
         hc, tj = ctx.autotune(n, n_h)[0]
     elif args.mfma > 0:
         return "k_lscv_units_mfma"
-    else:
-        hc = args.hc if args.hc > 0 else 16
-        tj = args.tj if getattr(args, "tj", -1) > 0 else 512
-    # a dense pass longer than one bounded launch (the default "launch_evals")
-    # runs as one persistent launch unless switched off
-    long = (0.5 * n * (n - 1.0) * n_h if evals is None else evals) > 4e12
     return f"k_lscv_units_f32_queue<{hc}, {tj}>" if long and getattr(args, "persistent", -1) != 0 \
         else f"k_lscv_units_f32<{hc}>"
 

@@ -153,8 +153,11 @@ kde_status kde_ctx_set_precision(kde_ctx* ctx, kde_prec prec);
  *                  kde_autotune measured fastest for the job's largest LSCV
  *                  column (tuning that shape on first use when the job holds
  *                  at least 1e13 pair-term evaluations; smaller jobs use a
- *                  cached decision or lscv_hc / lscv_tj).  Results are
- *                  bitwise those of any variant.
+ *                  cached decision or lscv_hc / lscv_tj).  With
+ *                  "persistent" and without "prune", jobs of at most
+ *                  "launch_evals" evaluations always use lscv_hc: their pass
+ *                  runs a block per work unit, which the tuner does not
+ *                  time.  Results are bitwise those of any variant.
  *   "prune"        1: LSCV tile pruning on sorted samples (mixed precision;
  *                  synchronous calls, kde_batch, the server and jobs).
  *                  Each LSCV column is sorted on the device (the pair

@@ -228,6 +228,10 @@ kde_status select_variant(kde_ctx* c, const kde_request* reqs, int32_t n_req) {
     }
   }
   if (n_best == 0) return KDE_OK;
+  // a dense pass within one launch runs a block per unit in place of the
+  // persistent launch (lscv_queue_form): not the kernel that the trials time,
+  // and of one tile size
+  if (c->opt_persistent && !c->opt_prune && total <= c->opt_launch_evals) return KDE_OK;
   auto hit = c->tune_cache.find(shape_key(n_best, nh_best));
   TuneChoice t;
   if (hit != c->tune_cache.end()) {
