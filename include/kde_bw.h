@@ -117,8 +117,10 @@ kde_status kde_ctx_set_precision(kde_ctx* ctx, kde_prec prec);
  *   "lscv_hc"      bandwidths per pass of the LSCV pair kernel (8, 16 or 32)
  *   "lscv_tj"      samples per LDS tile of the persistent dense LSCV sweep
  *                  (256, 512 or 1024; other than 512 only with lscv_hc 16,
- *                  else the pass falls back to sliced launches).  Results
- *                  are bitwise those of any tile size.
+ *                  else the pass falls back to sliced launches).  Passes of
+ *                  at most "launch_evals" evaluations run a block per work
+ *                  unit, with tiles of 512 whatever it says.  Results are
+ *                  bitwise those of any tile size.
  *   "seg"          j-range per work item, rounded to the tile (0 = whole row)
  *   "launch_evals" pair-term evaluations per kernel launch (launch splitting)
  *   "fp64_kappa"   mixed precision: kappa above which a plug-in stage is re-run
