@@ -224,16 +224,17 @@ struct ColDesc {
   int n_items;          // LSCV partial-sum slots a bandwidth (work items x pieces)
   int n_items_psi;      // psi partial-sum slots (work items x psi_groups)
   int grid_kind;        // kGridExplicit / kGridPaper / kGridLogRot
-  int pad0;
+  int lscv_piece;       // samples j an LSCV partial-sum slot, where items are cut into pieces (0: a unit has one slot)
   double grid_lo, grid_hi;
 };
 
 // One block of a pair kernel: the samples i in [row*kBI, row*kBI + kBI) (psi
-// with chunk 1: [row*64, row*64 + 64)) of column `col` against j in [j_begin, j_end) (a multiple of 64 long; a
-// column's last unit may run past n into the +inf padding).  `item` is the
-// partial-sum slot within the column (its work item, times the units an item
-// is cut into, plus the unit), `chunk` the bandwidth chunk (LSCV)
-// or the psi geometry (0: rows of kBI samples, 1: of 64).
+// with chunk 1: [row*64, row*64 + 64)) of column `col` against j in
+// [j_begin, j_end) (a multiple of 64 long; a column's last unit may run past n
+// into the +inf padding).  `item` is the (first) partial-sum slot within the
+// column (its work item, times the slots of an item, plus the unit's place in
+// it), `chunk` the bandwidth chunk (LSCV) or the psi geometry (0: rows of kBI
+// samples, 1: of 64).
 struct Unit {
   int col, row, j_begin, j_end, item, chunk;
 };

@@ -94,7 +94,8 @@ void make_units(kde_job* j) {
   j->lscv_c.clear();
   kde::psi_units_of(j->plan, 0, j->psi_u, j->psi_c);
   // with tile pruning the sweep units name the pruned-sweep descriptor (2)
-  kde::lscv_units_of(j->plan, j->plan.prune ? 2 : 0, j->lscv_u, j->lscv_c);
+  // units a piece: the saved cursor counts them
+  kde::lscv_units_of(j->plan, j->plan.prune ? 2 : 0, j->lscv_u, j->lscv_c, false);
 }
 
 uint64_t ckpt_bytes(const kde_job* j) {

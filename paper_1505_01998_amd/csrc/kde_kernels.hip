@@ -484,9 +484,18 @@ __global__ __launch_bounds__(kThreads) void k_stats_one(const ColDesc* __restric
   stats_final(c, next, hc);
 }
 
-// Where a unit's sweep ends: its j-range, cut to the runs of kRun that hold a
+// Where a sweep over j ends: its range, cut to the runs of kRun that hold a
 // sample (what lies beyond n is padding and adds exact zeros).
-__device__ __forceinline__ int unit_end(const Unit& u, int n) { return min(u.j_end, (n + kRun - 1) / kRun * kRun); }
+__device__ __forceinline__ int sweep_end(int j_end, int n) { return min(j_end, (n + kRun - 1) / kRun * kRun); }
+__device__ __forceinline__ int unit_end(const Unit& u, int n) { return sweep_end(u.j_end, n); }
+
+// Samples j of an LSCV unit that share a partial-sum slot: a whole item of a
+// column cut into pieces has a slot a piece, and its unit sweeps them one
+// after the other, each from cleared sums, so that a slot holds the same bits
+// as from a unit of its own.
+__device__ __forceinline__ int slot_step(const Unit& u, const ColDesc& c) {
+  return c.lscv_piece ? c.lscv_piece : u.j_end - u.j_begin;
+}
 
 // ------------------------------------------------------------------ psi pair kernels
 // Mixed form.  The samples are pre-scaled by 1/g (y = x / g, one O(n) pass
@@ -853,7 +862,7 @@ __device__ __forceinline__ void lscv_run(const float4* __restrict__ tile, int jl
 
 // One LSCV work unit of the vector-ALU sweep: the unit's row of 256 samples
 // i against its j-range, for the HC bandwidths of its chunk; the block's
-// FP64 partial sums go to the unit's own slots.  TJ: samples per LDS tile
+// FP64 partial sums go to the unit's own slots (slot_step).  TJ: samples per LDS tile
 // (256, 512 or 1024; a unit's j-range is a multiple of kRun, so a tile may
 // end partly full).  The tile size changes only how often the block stages
 // and synchronises: every lane still folds its terms in runs of 64 j in
@@ -873,41 +882,44 @@ __device__ __forceinline__ void lscv_unit_f32(const ColDesc* __restrict__ cols, 
   const int wave_i0 = row0 + wave * 64;
   const float* cc = c.c32 + u.chunk * HC;
   float ck[HC];
-  double a1[HC], a2[HC];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) {
-    ck[k] = uniform_f32(cc[k]);
-    a1[k] = a2[k] = 0.0;
-  }
-  const int j_end = unit_end(u, n);
-  for (int t0 = u.j_begin; t0 < j_end; t0 += TJ) {
-    const int te = min(t0 + TJ, j_end);
-    __syncthreads();
-    for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
-    __syncthreads();
-    int js = max(t0, wave_i0);
-    if (js < te) {
-      if (js == wave_i0) {
-        lscv_run<HC, true>(tile, js - t0, js, xi, i, ck, a1, a2);
-        js += kRun;
+  for (int k = 0; k < HC; ++k) ck[k] = uniform_f32(cc[k]);
+  const int step = slot_step(u, c);
+  for (int p0 = u.j_begin, slot = u.item; p0 < u.j_end; p0 += step, ++slot) {
+    if (p0 > u.j_begin) __syncthreads();  // red has been read
+    double a1[HC], a2[HC];
+#pragma unroll
+    for (int k = 0; k < HC; ++k) a1[k] = a2[k] = 0.0;
+    const int j_end = sweep_end(p0 + step, n);
+    for (int t0 = p0; t0 < j_end; t0 += TJ) {
+      const int te = min(t0 + TJ, j_end);
+      __syncthreads();
+      for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
+      __syncthreads();
+      int js = max(t0, wave_i0);
+      if (js < te) {
+        if (js == wave_i0) {
+          lscv_run<HC, true>(tile, js - t0, js, xi, i, ck, a1, a2);
+          js += kRun;
+        }
+        for (; js < te; js += kRun) lscv_run<HC, false>(tile, js - t0, js, xi, i, ck, a1, a2);
       }
-      for (; js < te; js += kRun) lscv_run<HC, false>(tile, js - t0, js, xi, i, ck, a1, a2);
     }
-  }
-  const bool valid = i < n;
-  double v[2 * HC];
+    const bool valid = i < n;
+    double v[2 * HC];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) {
-    v[2 * k] = valid ? a1[k] : 0.0;
-    v[2 * k + 1] = valid ? a2[k] : 0.0;
-  }
-  wave_sums(v, red[wave], lane);
-  __syncthreads();
-  if (tid < 2 * HC) {
-    const int h = u.chunk * HC + (tid >> 1);
-    if (h < c.n_h) {
-      const double v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
-      c.part[(int64_t)(2 * h + (tid & 1)) * c.n_items + u.item] = v;
+    for (int k = 0; k < HC; ++k) {
+      v[2 * k] = valid ? a1[k] : 0.0;
+      v[2 * k + 1] = valid ? a2[k] : 0.0;
+    }
+    wave_sums(v, red[wave], lane);
+    __syncthreads();
+    if (tid < 2 * HC) {
+      const int h = u.chunk * HC + (tid >> 1);
+      if (h < c.n_h) {
+        const double v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+        c.part[(int64_t)(2 * h + (tid & 1)) * c.n_items + slot] = v;
+      }
     }
   }
 }
@@ -1243,43 +1255,47 @@ __global__ __launch_bounds__(kThreads) void k_lscv_units_f64(const ColDesc* __re
   const double xi = (i < n) ? x[i] : 0.0;
   const int wave_i0 = row0 + wave * 64;
   const double* cc = c.c64 + u.chunk * HC;
-  double ck[HC], s1[HC], s2[HC];
+  double ck[HC];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) {
-    ck[k] = cc[k];
-    s1[k] = s2[k] = 0.0;
-  }
+  for (int k = 0; k < HC; ++k) ck[k] = cc[k];
   if (tid < 3 * 64) tab[tid] = kExp2Tab[0][tid];
-  const int j_end = unit_end(u, n);
-  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
-    const int te = min(t0 + kBJ, j_end);
-    __syncthreads();
-    for (int q = tid; q < (te - t0) / 2; q += kThreads)
-      reinterpret_cast<double2*>(tile)[q] = reinterpret_cast<const double2*>(x + t0)[q];
-    __syncthreads();
-    int js = max(t0, wave_i0);
-    if (js < te) {
-      if (js == wave_i0) {
-        lscv_run64<HC, true>(tile, js - t0, js, xi, i, ck, tab, s1, s2);
-        js += kRun;
-      }
-      for (; js < te; js += kRun) lscv_run64<HC, false>(tile, js - t0, js, xi, i, ck, tab, s1, s2);
-    }
-  }
-  const bool valid = i < n;
-  double v[2 * HC];
+  const int step = slot_step(u, c);
+  for (int p0 = u.j_begin, slot = u.item; p0 < u.j_end; p0 += step, ++slot) {
+    if (p0 > u.j_begin) __syncthreads();  // red has been read
+    double s1[HC], s2[HC];
 #pragma unroll
-  for (int k = 0; k < HC; ++k) {
-    v[2 * k] = valid ? s1[k] : 0.0;
-    v[2 * k + 1] = valid ? s2[k] : 0.0;
-  }
-  wave_sums(v, red[wave], lane);
-  __syncthreads();
-  if (tid < 2 * HC) {
-    const int h = u.chunk * HC + (tid >> 1);
-    if (h < c.n_h) {
-      const double v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
-      c.part[(int64_t)(2 * h + (tid & 1)) * c.n_items + u.item] = v;
+    for (int k = 0; k < HC; ++k) s1[k] = s2[k] = 0.0;
+    const int j_end = sweep_end(p0 + step, n);
+    for (int t0 = p0; t0 < j_end; t0 += kBJ) {
+      const int te = min(t0 + kBJ, j_end);
+      __syncthreads();
+      for (int q = tid; q < (te - t0) / 2; q += kThreads)
+        reinterpret_cast<double2*>(tile)[q] = reinterpret_cast<const double2*>(x + t0)[q];
+      __syncthreads();
+      int js = max(t0, wave_i0);
+      if (js < te) {
+        if (js == wave_i0) {
+          lscv_run64<HC, true>(tile, js - t0, js, xi, i, ck, tab, s1, s2);
+          js += kRun;
+        }
+        for (; js < te; js += kRun) lscv_run64<HC, false>(tile, js - t0, js, xi, i, ck, tab, s1, s2);
+      }
+    }
+    const bool valid = i < n;
+    double v[2 * HC];
+#pragma unroll
+    for (int k = 0; k < HC; ++k) {
+      v[2 * k] = valid ? s1[k] : 0.0;
+      v[2 * k + 1] = valid ? s2[k] : 0.0;
+    }
+    wave_sums(v, red[wave], lane);
+    __syncthreads();
+    if (tid < 2 * HC) {
+      const int h = u.chunk * HC + (tid >> 1);
+      if (h < c.n_h) {
+        const double v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+        c.part[(int64_t)(2 * h + (tid & 1)) * c.n_items + slot] = v;
+      }
     }
   }
 }
@@ -1374,42 +1390,46 @@ __global__ __launch_bounds__(kThreads) void k_lscv_units_mfma(const ColDesc* __r
   // B operand: k = lane / 32, col = lane % 32
   const int kb = lane >> 5, colb = lane & 31;
   const float bop = (kb == (colb >> 4)) ? c.c32[u.chunk * HC + (colb & 15)] : 0.f;
-  float a1 = 0.f, c1 = 0.f, a2 = 0.f, c2 = 0.f;
   const bool rows_full = wave_i0 + 64 <= n;
-  const int j_end = unit_end(u, n);
-  for (int t0 = u.j_begin; t0 < j_end; t0 += kBJ) {
-    const int te = min(t0 + kBJ, j_end);
-    __syncthreads();
-    for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
-    __syncthreads();
-    for (int js = max(t0, wave_i0); js < te; js += 16) {
-      float s1[4] = {0.f, 0.f, 0.f, 0.f}, s2[4] = {0.f, 0.f, 0.f, 0.f};
-      const bool clean = rows_full && js >= wave_i0 + 64 && js + 16 <= n;
-      if (clean)
-        mfma_group<false>(tile, js - t0, js, xa, xb, wave_i0, n, bop, lane, s1, s2);
-      else
-        mfma_group<true>(tile, js - t0, js, xa, xb, wave_i0, n, bop, lane, s1, s2);
-      kahan_add(a1, c1, (s1[0] + s1[1]) + (s1[2] + s1[3]));
-      kahan_add(a2, c2, (s2[0] + s2[1]) + (s2[2] + s2[3]));
+  const int step = slot_step(u, c);
+  for (int p0 = u.j_begin, slot = u.item; p0 < u.j_end; p0 += step, ++slot) {
+    if (p0 > u.j_begin) __syncthreads();  // red has been read
+    float a1 = 0.f, c1 = 0.f, a2 = 0.f, c2 = 0.f;
+    const int j_end = sweep_end(p0 + step, n);
+    for (int t0 = p0; t0 < j_end; t0 += kBJ) {
+      const int te = min(t0 + kBJ, j_end);
+      __syncthreads();
+      for (int q = tid; q < (te - t0) / 4; q += kThreads) tile[q] = reinterpret_cast<const float4*>(x + t0)[q];
+      __syncthreads();
+      for (int js = max(t0, wave_i0); js < te; js += 16) {
+        float s1[4] = {0.f, 0.f, 0.f, 0.f}, s2[4] = {0.f, 0.f, 0.f, 0.f};
+        const bool clean = rows_full && js >= wave_i0 + 64 && js + 16 <= n;
+        if (clean)
+          mfma_group<false>(tile, js - t0, js, xa, xb, wave_i0, n, bop, lane, s1, s2);
+        else
+          mfma_group<true>(tile, js - t0, js, xa, xb, wave_i0, n, bop, lane, s1, s2);
+        kahan_add(a1, c1, (s1[0] + s1[1]) + (s1[2] + s1[3]));
+        kahan_add(a2, c2, (s2[0] + s2[1]) + (s2[2] + s2[3]));
+      }
     }
-  }
-  // lanes l, l^16, l^32, l^48 hold the same bandwidth
-  double v1 = (double)a1 - (double)c1, v2 = (double)a2 - (double)c2;
-  v1 += __shfl_xor(v1, 16, 64);
-  v2 += __shfl_xor(v2, 16, 64);
-  v1 += __shfl_xor(v1, 32, 64);
-  v2 += __shfl_xor(v2, 32, 64);
-  if (lane < HC) {
-    red[wave][lane][0] = v1;
-    red[wave][lane][1] = v2;
-  }
-  __syncthreads();
-  if (tid < 2 * HC) {
-    const int hk = tid >> 1, w = tid & 1;
-    const int h = u.chunk * HC + hk;
-    if (h < c.n_h) {
-      const double v = ((red[0][hk][w] + red[1][hk][w]) + red[2][hk][w]) + red[3][hk][w];
-      c.part[(int64_t)(2 * h + w) * c.n_items + u.item] = v;
+    // lanes l, l^16, l^32, l^48 hold the same bandwidth
+    double v1 = (double)a1 - (double)c1, v2 = (double)a2 - (double)c2;
+    v1 += __shfl_xor(v1, 16, 64);
+    v2 += __shfl_xor(v2, 16, 64);
+    v1 += __shfl_xor(v1, 32, 64);
+    v2 += __shfl_xor(v2, 32, 64);
+    if (lane < HC) {
+      red[wave][lane][0] = v1;
+      red[wave][lane][1] = v2;
+    }
+    __syncthreads();
+    if (tid < 2 * HC) {
+      const int hk = tid >> 1, w = tid & 1;
+      const int h = u.chunk * HC + hk;
+      if (h < c.n_h) {
+        const double v = ((red[0][hk][w] + red[1][hk][w]) + red[2][hk][w]) + red[3][hk][w];
+        c.part[(int64_t)(2 * h + w) * c.n_items + slot] = v;
+      }
     }
   }
 }

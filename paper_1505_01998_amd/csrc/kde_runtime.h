@@ -51,7 +51,7 @@ struct ColPlan {
   std::vector<double> grid_h;  // explicit grid
   ColItems psi_items, lscv_items;
   int psi_groups = 1;   // psi units (and partial-sum slots) per work item: 1, or kPsiGroups of 64 samples i
-  int lscv_pieces = 1;  // LSCV units (and partial-sum slots) per work item and bandwidth chunk
+  int lscv_pieces = 1;  // LSCV partial-sum slots per work item and bandwidth
   // tile pruning (mixed form, LSCV): a sorted copy of the column, the first
   // j-tile of every row as "near" items, and per-chunk cut distances
   bool prune = false;
@@ -103,6 +103,7 @@ struct IterPlan {
   std::vector<int> ids_lscv_prep;
   std::vector<Unit> lscv_units;
   std::vector<UnitCost> lscv_cost;
+  bool lscv_whole = false;  // lscv_units holds whole units that split_lscv_units may cut (server)
   int lscv_groups[kQueueGroups + 1] = {};  // persistent form: group g is lscv_units [lscv_groups[g], [g + 1])
   std::vector<RowDesc> lscv_rows;
   std::vector<int> ids_lscv_final;
@@ -326,8 +327,9 @@ void bind_column(const ColPlan& p, char* block, const void* raw, DevState* st, C
 // to an executor plan; host_raw / host grid are uploaded into the block.
 // extra_id: with tile pruning, the index of the column's two extra
 // descriptors (near tiles, pruned sweep) in the pass's column table, else -1.
+// whole: the pass runs whole LSCV units (runs_whole).
 void add_full_column(const kde_ctx* c, const ColPlan& p, const ColDesc& d, int id, const void* host_raw,
-                     IterPlan& it, int extra_id = -1);
+                     IterPlan& it, int extra_id, bool whole);
 // Tile pruning: the two extra descriptors of a pruned column (near tiles:
 // sorted copy and near-tile slab; pruned sweep: sorted copy and main slab),
 // and the column's set-up in a pass (sort, near-tile units and rows, cut
@@ -336,7 +338,20 @@ void prune_descs(const ColPlan& p, const ColDesc& d, ColDesc& nd, ColDesc& sd);
 void add_prune_setup(const ColPlan& p, const ColDesc& d, int id, int extra_id, IterPlan& it);
 // Pieces used by the server to schedule a column's work over several passes.
 void psi_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost);
-void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost);
+// whole: a unit an item and chunk; else one a piece.
+void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost, bool whole);
+// A pass runs whole units, whose blocks sweep an item's pieces one after the
+// other into the same slots (an eighth of the units at most to plan and
+// upload), where there are 1024 of them (the blocks the chip holds at once)
+// and over 6144 pieces (twice what a single column is cut to fill the chip
+// with).  Units a piece against whole ones, 100 bandwidths: 4 columns of n =
+// 3000 (1176 whole units, 9408 pieces) 0.42 and 0.38 ms, 8 of them 0.76 and
+// 0.69, 100 of them 8.9 and 7.5, 1000 of them 107 and 77; 40 of n = 1000
+// (1680, 13440) 0.97 and 0.93; at 16 of n = 1000 (672, 5376) both 0.43.
+constexpr size_t kWholeUnits = 1024, kSplitUnits = 6144;
+inline bool runs_whole(size_t units, size_t pieces) { return units >= kWholeUnits && pieces > kSplitUnits; }
+// Cuts a pass's whole LSCV units into a unit a piece where they are few.
+void split_lscv_units(IterPlan& it);
 void begin_stage(const ColPlan& p, int id, int stage, IterPlan& it);
 void lscv_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows);
 void init_state(const ColPlan& p, double fp64_kappa, DevState& h);

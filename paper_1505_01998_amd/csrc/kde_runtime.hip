@@ -90,7 +90,7 @@ void IterPlan::clear() {
   prune_units.clear();
   prune_cost.clear();
   max_stat_blocks = 1;
-  psi_shared = psi_two_stage = false;
+  psi_shared = psi_two_stage = lscv_whole = false;
 }
 
 // ---- argument checks
@@ -357,6 +357,7 @@ void bind_column(const ColPlan& p, char* b, const void* raw, DevState* st, ColDe
   d.n_items = (int)p.lscv_items.pairs.size() * p.lscv_pieces;
   d.n_items_psi = (int)p.psi_items.pairs.size() * p.psi_groups;
   d.grid_kind = p.grid_kind;
+  d.lscv_piece = p.lscv_pieces > 1 ? kBJ / p.lscv_pieces : 0;
   d.grid_lo = p.grid_lo;
   d.grid_hi = p.grid_hi;
 }
@@ -398,17 +399,46 @@ void psi_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<Un
     }
 }
 
-void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost) {
-  const int P = p.lscv_pieces;
+void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<UnitCost>& cost, bool whole) {
+  const int slots = p.lscv_pieces, P = whole ? 1 : slots;
   for (size_t it = 0; it < p.lscv_items.pairs.size(); ++it)
     for (int q = 0; q < P; ++q) {
       int jb, je;
       const double pairs = piece_of(p.lscv_items, it, p.n, P, q, jb, je);
       for (int ch = 0; ch < p.n_chunks; ++ch) {
-        u.push_back(Unit{id, p.lscv_items.row[it], jb, je, (int)it * P + q, ch});
+        u.push_back(Unit{id, p.lscv_items.row[it], jb, je, (int)it * slots + q, ch});
         cost.push_back(UnitCost{pairs, pairs * std::min(p.hc, p.n_h - ch * p.hc)});
       }
     }
+}
+
+void split_lscv_units(IterPlan& it) {
+  const auto step_of = [&](const Unit& w) {
+    const int piece = it.cols[w.col].lscv_piece;
+    return piece ? piece : w.j_end - w.j_begin;
+  };
+  size_t pieces = 0;
+  for (const Unit& w : it.lscv_units) pieces += (w.j_end - w.j_begin) / step_of(w);
+  if (pieces == it.lscv_units.size() || runs_whole(it.lscv_units.size(), pieces)) return;
+  std::vector<Unit> u;
+  std::vector<UnitCost> cost;
+  for (size_t k = 0; k < it.lscv_units.size(); ++k) {
+    const Unit& w = it.lscv_units[k];
+    const int step = step_of(w);
+    if (step == w.j_end - w.j_begin) {
+      u.push_back(w);
+      cost.push_back(it.lscv_cost[k]);
+      continue;
+    }
+    const double valid = it.lscv_cost[k].evals / it.lscv_cost[k].pairs;  // bandwidths of the chunk
+    for (int jb = w.j_begin, slot = w.item; jb < w.j_end; jb += step, ++slot) {
+      const double pairs = item_pairs(it.cols[w.col].n, w.row, jb, jb + step);
+      u.push_back(Unit{w.col, w.row, jb, jb + step, slot, w.chunk});
+      cost.push_back(UnitCost{pairs, pairs * valid});
+    }
+  }
+  it.lscv_units.swap(u);
+  it.lscv_cost.swap(cost);
 }
 
 void begin_stage(const ColPlan& p, int id, int stage, IterPlan& it) {
@@ -450,7 +480,7 @@ void add_prune_setup(const ColPlan& p, const ColDesc& d, int id, int extra_id, I
 }
 
 void add_full_column(const kde_ctx* c, const ColPlan& p, const ColDesc& d, int id, const void* host_raw,
-                     IterPlan& it, int extra_id) {
+                     IterPlan& it, int extra_id, bool whole) {
   if ((int)it.cols.size() <= id) it.cols.resize(id + 1);
   it.cols[id] = d;
   if (p.raw_in_block) it.uploads.push_back(Upload{(void*)d.raw, host_raw, p.raw_bytes});
@@ -477,9 +507,9 @@ void add_full_column(const kde_ctx* c, const ColPlan& p, const ColDesc& d, int i
     it.ids_lscv_prep.push_back(id);
     if (p.prune && extra_id >= 0) {
       add_prune_setup(p, d, id, extra_id, it);
-      lscv_units_of(p, extra_id + 1, it.prune_units, it.prune_cost);
+      lscv_units_of(p, extra_id + 1, it.prune_units, it.prune_cost, whole);
     } else {
-      lscv_units_of(p, id, it.lscv_units, it.lscv_cost);
+      lscv_units_of(p, id, it.lscv_units, it.lscv_cost, whole);
     }
     lscv_rows_of(p, d, it.lscv_rows);
     it.ids_lscv_final.push_back(id);
@@ -745,6 +775,7 @@ kde_status pack_pass(kde_ctx* c, IterPlan& it, PassLayout& L) {
     it.psi_narrow[q] = sort_psi_units(it.psi_units[q], it.psi_cost[q]);
     it.psi_cond_narrow[q] = sort_psi_units(it.psi_cond_units[q], it.psi_cond_cost[q]);
   }
+  if (it.lscv_whole) split_lscv_units(it);
   sort_units(it.lscv_units, it.lscv_cost);
   if (lscv_queue_form(c, it)) {
     group_units(it.lscv_units, it.lscv_cost, it.cols, it.lscv_groups);
@@ -1146,13 +1177,20 @@ kde_status run_requests(kde_ctx* c, const kde_request* reqs, int32_t n_req, std:
   c->h_st = reinterpret_cast<DevState*>(hs);
   kde::IterPlan& it = c->iter;
   it.clear();
+  size_t units = 0, pieces = 0;
+  for (const kde::ColPlan& p : c->plans)
+    if (p.lscv && !p.prune) {
+      units += p.lscv_items.pairs.size() * p.n_chunks;
+      pieces += p.lscv_items.pairs.size() * p.n_chunks * p.lscv_pieces;
+    }
+  const bool whole = kde::runs_whole(units, pieces);
   int extra = n_cols;  // tile pruning: two more descriptors per pruned column
   for (int k = 0; k < n_cols; ++k) {
     const kde::ColPlan& p = c->plans[k];
     const kde_request& r = reqs[c->plan_req[k]];
     ColDesc d;
     kde::bind_column(p, c->blocks.p + at[k], r.x.data, c->st.p + k, d);
-    kde::add_full_column(c, p, d, k, r.x.data, it, p.prune ? extra : -1);
+    kde::add_full_column(c, p, d, k, r.x.data, it, p.prune ? extra : -1, whole);
     if (p.prune) extra += 2;
     kde::init_state(p, c->opt_fp64_kappa, c->h_st[k]);
   }

@@ -268,7 +268,7 @@ void Server::loop() {
       init_state(r->plan, ctx->opt_fp64_kappa, h_st[r->slot]);
       (void)hipMemcpyAsync(st.p + r->slot, h_st + r->slot, sizeof(DevState), hipMemcpyHostToDevice, ctx->stream);
       psi_units_of(r->plan, r->slot, r->psi_u, r->psi_c);
-      lscv_units_of(r->plan, r->slot, r->lscv_u, r->lscv_c);
+      lscv_units_of(r->plan, r->slot, r->lscv_u, r->lscv_c, true);
       r->stage = r->plan.stages == 3 ? 0 : 1;
       r->remaining = 0.0;
       for (const UnitCost& u : r->psi_c) r->remaining += u.evals * (3 - r->stage);
@@ -295,6 +295,7 @@ void Server::loop() {
     // constant tau) a request's remaining work counts as
     // remaining / (1 + waited / tau), so long-waiting large requests move up
     it.clear();
+    it.lscv_whole = true;
     top = 0;
     for (auto& r : active) top = std::max(top, r->slot + 1);
     it.cols.assign((ctx->opt_prune ? 3 : 1) * (size_t)top, ColDesc());
