@@ -247,15 +247,26 @@ __global__ __launch_bounds__(kThreads / IB) void k_HZ_units_f32(const float* __r
 // loads through the scalar cache) and enter the arithmetic as scalar
 // operands, with no tile and no barrier.  Measured at n = 1e5, d = 8: 20%
 // faster than the tiled kernel; at D <= 3 the tiled kernel is faster.
-template <int D, bool MASK>
+// G samples j a step.  RAISED: their exponentials are issued together at
+// raised priority; else the compiler places them.  D = 8: eight a step (a
+// dimension's eight come in one load, and a wave alone on its SIMD has eight
+// independent terms), raised.  D = 16, where an exponential is 8 of the 100
+// cycles of a pair: four a step, raised, while the waves are few; with the
+// chip full raising costs more than it gives, and eight are left to the
+// compiler.  All forms add the same terms in the same order.  One pair at a
+// time / four a step, raised, everywhere / this rule: d = 8, n = 300, 64
+// matrices 2.89 / 3.29 / 2.70 ms, n = 2500 4.99 / 5.37 / 4.36, n = 1.3e5, 4
+// matrices 12.9 / 11.3 / 11.2; d = 12, n = 5000, 64 8.40 / 6.66 / 6.64, n =
+// 6e4, 4 4.94 / 5.54 / 4.92, n = 1.3e5, 4 21.1 / 24.0 / 21.1.
+template <int D, int G, bool RAISED, bool MASK>
 __device__ __forceinline__ void hz_run_s(const float* __restrict__ z, int npad, int jg, const float (&zi)[D], int i,
                                        float& a1, float& c1, float& a2, float& c2) {
   float r1 = 0.f, r2 = 0.f;
-#pragma unroll 2
-  for (int q = 0; q < kMdRun; q += kExpGroup) {
-    float e[kExpGroup];
+#pragma unroll 8 / G
+  for (int q = 0; q < kMdRun; q += G) {
+    float e[G];
 #pragma unroll
-    for (int u = 0; u < kExpGroup; ++u) {
+    for (int u = 0; u < G; ++u) {
       float s = 0.f;
 #pragma unroll
       for (int a = 0; a < D; ++a) {
@@ -265,19 +276,24 @@ __device__ __forceinline__ void hz_run_s(const float* __restrict__ z, int npad, 
       if (MASK) s = (jg + q + u > i) ? s : __builtin_inff();
       e[u] = -s;
     }
-    exp2_group(e);
+    if constexpr (RAISED) {
+      exp2_group(e);
+    } else {
 #pragma unroll
-    for (int u = 0; u < kExpGroup; ++u) {
+      for (int u = 0; u < G; ++u) e[u] = __builtin_amdgcn_exp2f(e[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
       r1 += e[u];
       r2 = __builtin_fmaf(e[u], e[u], r2);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (RAISED) __builtin_amdgcn_sched_barrier(0);
   }
   md_fold(a1, c1, r1);
   md_fold(a2, c2, r2);
 }
 
-template <int D>
+template <int D, int G, bool RAISED>
 __global__ __launch_bounds__(kThreads) void k_HZ_units_f32s(const float* __restrict__ z, int npad,
                                                            const MdState* __restrict__ st,
                                                            const Unit* __restrict__ units, int u0,
@@ -298,10 +314,10 @@ __global__ __launch_bounds__(kThreads) void k_HZ_units_f32s(const float* __restr
   int js = __builtin_amdgcn_readfirstlane(max(u.j_begin, wave_i0));
   const int je = __builtin_amdgcn_readfirstlane(u.j_end);
   if (js < je && js == wave_i0) {
-    hz_run_s<D, true>(z, npad, js, zi, i, a1, c1, a2, c2);
+    hz_run_s<D, G, RAISED, true>(z, npad, js, zi, i, a1, c1, a2, c2);
     js += kMdRun;
   }
-  for (; js < je; js += kMdRun) hz_run_s<D, false>(z, npad, js, zi, i, a1, c1, a2, c2);
+  for (; js < je; js += kMdRun) hz_run_s<D, G, RAISED, false>(z, npad, js, zi, i, a1, c1, a2, c2);
   const bool valid = i < n;
   const double v1 = md_wave_sum(valid ? (double)a1 - (double)c1 : 0.0);
   const double v2 = md_wave_sum(valid ? (double)a2 - (double)c2 : 0.0);
@@ -389,14 +405,24 @@ __global__ void k_H_final(const MdState* st, const HDesc* hd, int m, const doubl
 // Two samples a lane from as many items as fill the chip's 8192 waves (8 a
 // SIMD) with their two waves each.
 constexpr int kIB2Items = 4096;
+// D = 16: fewer items leave the chip's 8192 waves short of work (four waves an
+// item).  n = 12000 (600 items), 8 matrices: raised 1.10 ms, not 1.22; n =
+// 25000 (2400), 4: 1.40 and 1.39; n = 6e4 (13,900), 4: 5.58 and 4.91.
+constexpr int kRaisedItems = 2048;
 
 void launch_HZ(hipStream_t s, int D, bool f64, const float* z32, const double* z64, int npad, const MdState* st,
                const Unit* units, int u0, int cnt, double* part, int n_items) {
 #define KDE_HZ_CASE(DD)                                                                                  \
   if (f64)                                                                                               \
     k_HZ_units_f64<DD><<<cnt, kThreads, 0, s>>>(z64, npad, st, units, u0, part, n_items);                \
-  else if constexpr (DD >= 8)                                                                            \
-    k_HZ_units_f32s<DD><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);               \
+  else if constexpr (DD == 8)                                                                            \
+    k_HZ_units_f32s<8, 8, true><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);       \
+  else if constexpr (DD == 16) {                                                                         \
+    if (n_items < kRaisedItems)                                                                          \
+      k_HZ_units_f32s<16, 4, true><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);    \
+    else                                                                                                 \
+      k_HZ_units_f32s<16, 8, false><<<cnt, kThreads, 0, s>>>(z32, npad, st, units, u0, part, n_items);   \
+  }                                                                                                      \
   else if (n_items >= kIB2Items)                                                                         \
     k_HZ_units_f32<DD, 2><<<cnt, kThreads / 2, 0, s>>>(z32, npad, st, units, u0, part, n_items);         \
   else                                                                                                   \
