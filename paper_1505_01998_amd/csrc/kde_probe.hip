@@ -59,10 +59,9 @@ __global__ __launch_bounds__(kProbeThreads) void k_issue(float a, float b, int i
 // The LSCV term mix: for a pair distance t and 16 bandwidth coefficients
 // c_k, e = exp2(t c_k), S1 += e, S2 += e e (one mul, one exp, one add, one
 // fma per term), then the next distance t + dt (one add per 16 terms).  With
-// t0 = dt = 0 every exponential is of zero.  Each term is issued in program
-// order behind a scheduling barrier, with the wave's priority raised from the
-// exponential to its consumers (the LSCV sweep itself groups its terms, which
-// is faster).
+// t0 = dt = 0 every exponential is of zero.  The terms go in groups, as in the
+// LSCV sweep: their products, their exponentials together at raised priority,
+// then their sums.
 __global__ __launch_bounds__(kProbeThreads) void k_issue_mix(float t0, float dt, float c0, int iters,
                                                              float* __restrict__ out) {
   constexpr int HC = 16;
@@ -79,12 +78,16 @@ __global__ __launch_bounds__(kProbeThreads) void k_issue_mix(float t0, float dt,
     for (int u = 0; u < 4; ++u) {
       t = t + dt;
 #pragma unroll
-      for (int k = 0; k < HC; ++k) {
-        __builtin_amdgcn_s_setprio(1);
-        const float e = __builtin_amdgcn_exp2f(t * ck[k]);
-        s1[k] += e;
-        s2[k] = __builtin_fmaf(e, e, s2[k]);
-        __builtin_amdgcn_s_setprio(0);
+      for (int k0 = 0; k0 < HC; k0 += kExpGroup) {
+        float e[kExpGroup];
+#pragma unroll
+        for (int k = 0; k < kExpGroup; ++k) e[k] = t * ck[k0 + k];
+        exp2_group(e);
+#pragma unroll
+        for (int k = 0; k < kExpGroup; ++k) {
+          s1[k0 + k] += e[k];
+          s2[k0 + k] = __builtin_fmaf(e[k], e[k], s2[k0 + k]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
     }
