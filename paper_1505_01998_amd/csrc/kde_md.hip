@@ -552,6 +552,16 @@ void launch_md_units(hipStream_t s, bool wide, const float* y32, const double* y
     k_md_units_f32<D, HC><<<cnt, kThreads, 0, s>>>(y32, npad, st, c32, units, u0, part, n_items, n_h);
 }
 
+// A pass of fewer units of 256 samples runs k_md_wide_f32's of 64.  Those pay
+// two barriers and an exchange of 2 HC sums a wave every 512 j, and fill the
+// chip's last round better, which holds 1024 blocks of 256 with HC = 16 (D <=
+// 4) and 2048 with HC = 8; the dearer a term, the less the exchange weighs.
+// Units of 256 against 64, ms a call: d = 3, n = 5e4, 96 bandwidths (1644
+// units) 13.7 and 13.1, 128 (2192) 16.8 and 17.4, 256 (4384) 32.7 and 34.6;
+// d = 8, n = 5e4, 128 (4384) 23.5 and 23.2, n = 3e4, 400 (5900) 23.1 and 23.6,
+// n = 5e4, 256 (8768) 45.1 and 46.0; d = 16, n = 5e4, 256 (8768) 58.0 and 56.7.
+size_t md_wide_units(int D) { return D <= 4 ? 1792 : (D <= 8 ? 5120 : 8192); }
+
 // bandwidths per block: fewer for wide samples (registers)
 int md_hc(int D, bool f64) { return f64 ? 4 : (D <= 4 ? 16 : 8); }
 
@@ -642,7 +652,7 @@ static kde_status run_md(kde_ctx* c, const kde_matrix& x, const double* h_grid, 
   const Split cut = f64 ? pick_split(c, n, (double)chunks, kFillLscv)
                         : Split{capped_seg(c, n, kSegRefHC, (double)chunks), 1};
   make_items(n, cut.pieces > 1 ? kBJ / cut.pieces : cut.seg, items);
-  const bool wide = !f64 && items.pairs.size() * (size_t)chunks < 8192;
+  const bool wide = !f64 && items.pairs.size() * (size_t)chunks < md_wide_units(D);
   const int groups = wide ? kBI / 64 : 1;
   const int n_items = (int)items.pairs.size() * groups;
   std::vector<Unit> units;

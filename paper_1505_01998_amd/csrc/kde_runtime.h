@@ -279,7 +279,10 @@ constexpr int kSegRefHC = 16;
 void make_items(int64_t n, int64_t seg, ColItems& out);
 // A column of fewer psi items than this runs them as units of 64 samples i:
 // the blocks of 256 would fill less than four rounds of the 2048 that the
-// chip holds (n < 3.4e5 at the default launch size).
+// chip holds (n < 3.4e5 at the default launch size).  Three stages in units of
+// 256 against 64: n = 1e5 (868 items) 3.68 and 2.81 ms, 2e5 (3038) 27.2 and
+// 26.5, 3e5 (6512) 59.4 and 59.3, 3.35e5 (8052) 73.8 and 74.2, 4e5 (11,326)
+// 104.4 and 106.0, 5e5 (17,442) 162 and 165.
 constexpr size_t kPsiWideItems = 8192;
 // Item length of a pass whose blocks evaluate `hc` terms per pair.
 int64_t pick_seg(const kde_ctx* c, int64_t n, int hc);
