@@ -227,7 +227,7 @@ typedef struct {
   int32_t pad0;
 } kde_tune_info;
 kde_status kde_autotune(kde_ctx* ctx, int64_t n, int32_t n_h, kde_tune_info* out);
-/* Measures the ceiling of the LSCV sweep's inner loop on this device: the
+/* Measures the rate of the LSCV sweep's inner loop on this device: the
  * kernel's own per-(pair, h) code (Section 4.5: the pair distance formed once
  * and reused for hc bandwidths; FP32 exp2, S1 add, S2 fma, 64-term runs
  * folded into FP64) repeated over one LDS tile staged once, without tile
@@ -235,8 +235,10 @@ kde_status kde_autotune(kde_ctx* ctx, int64_t n, int32_t n_h, kde_tune_info* out
  * pair-term evaluations per second: launches of R and 2R repetitions (~0.1
  * and ~0.25 s) timed with events on the context's stream, the rate taken
  * over the extra R of the second so that launch start and drain cancel.
- * The rate bounds what the sweep can
- * reach with this instruction mix.  It measures the mixed form's kernel
+ * A reference for the sweep, not a bound: blocks that start together keep in
+ * step (a grid of only the resident blocks runs 7% slower than this one, of
+ * eight times as many), while the sweep's uneven units drift apart, and a full
+ * sweep has measured up to 2% above it.  It measures the mixed form's kernel
  * whatever the context's precision.  KDE_E_INVAL for hc other than 8, 16,
  * 32; KDE_E_BUSY while a server runs. */
 kde_status kde_lscv_ceiling(kde_ctx* ctx, int32_t hc, double* evals_per_s);
@@ -442,7 +444,8 @@ kde_status kde_request_footprint(const kde_ctx* ctx, const kde_request* req, uin
  * (0 = whole rows, > 0 rounded up to a multiple of 512, < 0 = automatic under
  * the default launch size, shortened when the pass would hold too few work
  * units to fill the device, lengthened when it would exceed 2^24; the shortest
- * items of small passes are summed in up to 8 pieces).  Writes min(cap, count) items and sets *n_items = count.
+ * items of small passes are summed in up to 8 pieces).  Writes
+ * min(cap, count) items and sets *n_items = count.
  * Host-only.  KDE_E_INVAL for n outside [2, KDE_MAX_N], n_h outside
  * [0, KDE_MAX_NH], cap < 0, or NULL arrays with cap > 0. */
 kde_status kde_plan_items(int64_t n, int32_t n_h, int64_t seg, int32_t cap, int32_t* n_items, int32_t* row_begin,

@@ -27,7 +27,7 @@
 // accumulator (the LSCV sweep: a conversion and an FP64 add, which issue at
 // the unpacked FP32 rate, half the cost of a compensated FP32 fold) or a
 // Kahan-compensated FP32 one (the psi pass, two sums per 64 pairs).  Lane
-// accumulators are reduced in FP64 across the wave (butterfly shuffles), the
+// accumulators are reduced in FP64 across the wave (lane exchanges), the
 // block (LDS, fixed order) and the work items (a separate row-reduction
 // kernel, fixed order), so the result is deterministic and independent of
 // scheduling.  The FP64 form
@@ -809,8 +809,9 @@ __global__ __launch_bounds__(kPsiThreads) __attribute__((amdgpu_waves_per_eu(8))
 // pairs with.  Cycles a term and SIMD, n = 1e5 x 256 bandwidths, HC = 16: one
 // term at a time with its priority raised from the exponential to its sums
 // 16.9; groups of 2 15.1; of 4 14.96; of 8 15.1; the same groups without
-// raised priority 21.2, with the plain part raised instead 21.0.  Sum of the
-// parts: 8.1 + 3.125 plain at 2.0 + the runs' folds (0.27) = 14.6.  A column
+// raised priority 21.2, with the plain part raised instead 21.0.  Estimate
+// from the parts: 8.1 + 3.125 plain at 2.0 + the runs' folds (0.27) = 14.6 (the
+// persistent sweep of n = 1e6 takes 14.57).  A column
 // of n = 1e5, 256 bandwidths: 138.2 -> 121.9 ms (9.26 -> 10.50e12 terms/s),
 // every sum bitwise unchanged.
 // K0: the first bandwidth taken (the pruned sweep leaves out small ones).
@@ -974,8 +975,8 @@ __global__ void k_zero_ints(int* __restrict__ p, int n) {
   if (k < n) p[k] = 0;
 }
 
-// Ceiling of the sweep's inner loop on the part: lscv_run<HC, false> over one
-// LDS tile of kBJ samples staged once, `reps` times per block, with no further
+// Reference rate of the sweep's inner loop on the part: lscv_run<HC, false> over
+// one LDS tile of kBJ samples staged once, `reps` times per block, with no further
 // staging, barriers, masks or partial-sum writes (each wave stores one sum so
 // that nothing is dropped).  Evaluations per launch:
 // blocks x kThreads x reps x kBJ x HC.
@@ -1189,7 +1190,8 @@ __constant__ uint32_t kExp2Tab[3][64] = {
     },
 };
 
-// exp_cw's e^x with |r| <= ln(2) / 128: e^x = 2^(n >> 6) (T + T (r + r^2 q(r))),
+// exp_cw's e^x with |r| <= ln(2) / 128, by the table method of Tang (ACM Trans.
+// Math. Softw. 15, 1989): e^x = 2^(n >> 6) (T + T (r + r^2 q(r))),
 // T = 2^((n & 63) / 64) from the words of kExp2Tab in LDS (a row's 64 words lie
 // in 64 banks, so that lanes that differ read different banks), q of degree 3
 // with least maximal relative error in e^r (1.4e-18).  13 FP64 instructions

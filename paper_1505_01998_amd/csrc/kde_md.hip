@@ -565,9 +565,9 @@ size_t md_wide_units(int D) { return D <= 4 ? 1792 : (D <= 8 ? 5120 : 8192); }
 // bandwidths per block: fewer for wide samples (registers)
 int md_hc(int D, bool f64) { return f64 ? 4 : (D <= 4 ? 16 : 8); }
 
-void launch_md(hipStream_t s, int D, bool f64, bool wide, const float* y32, const double* y64, int npad, const MdState* st,
-               const float* c32, const double* c64, const Unit* units, int u0, int cnt, double* part, int n_items,
-               int n_h) {
+void launch_md(hipStream_t s, int D, bool f64, bool wide, const float* y32, const double* y64, int npad,
+               const MdState* st, const float* c32, const double* c64, const Unit* units, int u0, int cnt,
+               double* part, int n_items, int n_h) {
 #define KDE_MD_CASE(DD, HH)                                                                                  \
   launch_md_units<DD, HH>(s, wide, y32, y64, npad, st, c32, c64, units, u0, cnt, part, n_items, n_h);          \
   return

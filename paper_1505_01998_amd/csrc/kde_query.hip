@@ -194,9 +194,10 @@ __global__ __launch_bounds__(kThreads) void k_density_final(const ColDesc* __res
 // ---- range aggregates
 // Mills' ratio of the normal law, Q(s) / phi(s) for 0 <= s <= 40: with
 // t = 1 / (s + 5), M(s) = t P(y), P a polynomial of degree 22 in y, the affine
-// image of t in [-1, 1] (interpolation at the Chebyshev nodes computed with 60
-// digits; within 1.3e-17 of M, about 2e-16 with the rounding of its
-// evaluation).
+// image of t in [-1, 1] (the change of variable of Shepherd and Laframboise,
+// Math. Comp. 36, 1981, for erfc; the coefficients by interpolation at the
+// Chebyshev nodes with 60 digits; within 1.3e-17 of M, 5.1e-17 with the
+// coefficients rounded, about 2e-16 with the rounding of its evaluation).
 __device__ __forceinline__ double mills(double s) {
   const double d = s + 5.0;
   double t = __builtin_amdgcn_rcp(d);  // about 2^-23, then two Newton steps
@@ -265,7 +266,10 @@ __device__ __forceinline__ void wave_order() {
 // no branch), 15 for one that is not; the form before took Phi through the
 // library's erfc on three branches of phi_diff, which the lanes of a wave
 // shared (600 instructions a sample).  A call of n = 1e6 x 256 ranges: 3.99
-// -> 0.86 ms, error against 64 bits 1.4e-16 -> 1.3e-16 of COUNT and SUM.
+// -> 0.85 ms.  Error of a single tail Q(z), on average and in 2^-53 of it: 2.0
+// for z < 1, 1.8 below 3, 4.1 below 6, 15 below 12, 65 below 25 (through erfc:
+// 0.8, 3.4, 14, 53, 227, nearly all of one sign); of COUNT and SUM in that call
+// 1.4e-16 before, 1.5e-16 now.
 template <bool FULL>
 __global__ __launch_bounds__(kThreads) void k_range_f64(const ColDesc* __restrict__ col, const double* __restrict__ lo,
                                                         const double* __restrict__ hi, double h, int piece_len,
@@ -361,7 +365,8 @@ __global__ __launch_bounds__(kThreads) void k_range_final(const ColDesc* __restr
   }
 }
 
-// pieces so that a launch has about 4096 blocks, each piece at least `least` samples
+// pieces so that a launch has about 4096 blocks, each piece at least `least`
+// samples
 int pieces_for(int64_t n, int64_t other_blocks, int64_t least = 4096) {
   const int64_t want = std::max<int64_t>(1, 4096 / std::max<int64_t>(1, other_blocks));
   const int64_t most = std::max<int64_t>(1, n / least);
@@ -424,8 +429,8 @@ kde_status kde_density(kde_ctx* c, kde_column x, double h, const double* points,
   if (f64)
     kde::k_density_f64<<<grid, kde::kThreads, 0, c->stream>>>(dcol, dq, m, h, piece_len, pieces, dpart);
   else if (qblocks * pieces < kde::kDensityWide)
-    kde::k_density_wide_f32<<<dim3((m + 63) / 64, pieces), 64 * kde::kWideWaves, 0, c->stream>>>(dcol, dq, m, h, piece_len,
-                                                                                               pieces, dpart);
+    kde::k_density_wide_f32<<<dim3((m + 63) / 64, pieces), 64 * kde::kWideWaves, 0, c->stream>>>(
+        dcol, dq, m, h, piece_len, pieces, dpart);
   else
     kde::k_density_f32<<<grid, kde::kThreads, 0, c->stream>>>(dcol, dq, m, h, piece_len, pieces, dpart);
   kde::k_density_final<<<m, kde::kThreads, 0, c->stream>>>(dcol, dpart, pieces, h, dout);

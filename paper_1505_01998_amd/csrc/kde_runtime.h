@@ -86,7 +86,8 @@ struct IterPlan {
   std::vector<ColDesc> cols;
   std::vector<int> ids_stats;
   std::vector<int> ids_begin[3], ids_finish[3];
-  std::vector<int> ids_scale[3];  // of ids_begin, the columns whose units read the scaled copy (mixed form, rows of 256)
+  // of ids_begin, the columns whose units read the scaled copy (mixed form, rows of 256)
+  std::vector<int> ids_scale[3];
   std::vector<Unit> psi_units[3];
   std::vector<UnitCost> psi_cost[3];
   // Columns added whole (add_full_column) run the same units in every stage
@@ -301,11 +302,11 @@ struct Split {
 // capped_seg, shortened (and the shortest items cut into pieces) until the
 // pass holds about `fill` units, `chunks` of them an item and piece.
 Split pick_split(const kde_ctx* c, int64_t n, double chunks, double fill);
-// Units that fill the chip with a few rounds of resident blocks.  Fewer leave a longer last round, more spend more on
-// each unit's start and end and on the planner: LSCV at 2048 / 3072 / 4096 /
-// 8192 units, n = 4e4 x 128: 11.3 / 11.0 / 10.7 / 11.0 ms a call, n = 5000 x
-// 128: 0.446 / 0.447 / 0.494 / 0.65 ms, 48 columns of n = 1e3 to 3e4: 45.4 /
-// 45.9 / 46.9 ms (the first three).
+// Units that fill the chip with a few rounds of resident blocks.  Fewer leave a
+// longer last round, more spend more on each unit's start and end and on the
+// planner: LSCV at 2048 / 3072 / 4096 / 8192 units, n = 4e4 x 128: 11.3 / 11.0
+// / 10.7 / 11.0 ms a call, n = 5000 x 128: 0.446 / 0.447 / 0.494 / 0.65 ms, 48
+// columns of n = 1e3 to 3e4: 45.4 / 45.9 / 46.9 ms (the first three).
 constexpr double kFillLscv = 3072.0;
 // Sets c->job_hc / job_mfma for a synchronous job over these requests: the
 // options, or with the autotune option the tuned vector-ALU variant of the

@@ -557,8 +557,8 @@ kde_status collect_timing(kde_ctx* c) {
 // Puts units largest first (the order blocks are dispatched in); results do
 // not depend on it, since every unit writes its own partial-sum slot.  Units
 // of one column come in that order; several columns' are dealt into 1024
-// classes of size in one pass (a comparison sort of the 290,000 psi and
-// 150,000 LSCV units of 48 columns cost more than their psi kernels).
+// classes of size in one pass (a comparison sort of the 290,000 psi units and
+// 150,000 LSCV pieces of 48 columns cost more than their psi kernels).
 // scatter: units of equal planned size are put in a fixed pseudo-random
 // order instead of (item, chunk) order.  With tile pruning their real cost
 // depends strongly on the chunk (small bandwidths skip most tiles), and
