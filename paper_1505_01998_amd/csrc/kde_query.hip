@@ -196,8 +196,10 @@ __global__ __launch_bounds__(kThreads) void k_density_final(const ColDesc* __res
 // t = 1 / (s + 5), M(s) = t P(y), P a polynomial of degree 22 in y, the affine
 // image of t in [-1, 1] (the change of variable of Shepherd and Laframboise,
 // Math. Comp. 36, 1981, for erfc; the coefficients by interpolation at the
-// Chebyshev nodes with 60 digits; within 1.3e-17 of M, 5.1e-17 with the
-// coefficients rounded, about 2e-16 with the rounding of its evaluation).
+// Chebyshev nodes with 60 digits, within 1.3e-17 of M).  The first six are
+// rounded so that phi M, whose kInvSqrt2Pi is 0.56 2^-53 too large, comes out
+// within 0.25 2^-53 of Q below s = 3 and 1.2 below 10 before the evaluation's
+// own rounding.
 __device__ __forceinline__ double mills(double s) {
   const double d = s + 5.0;
   double t = __builtin_amdgcn_rcp(d);  // about 2^-23, then two Newton steps
@@ -221,11 +223,11 @@ __device__ __forceinline__ double mills(double s) {
   p = __builtin_fma(p, y, -0.0013319023014207816);
   p = __builtin_fma(p, y, 0.002236503981011224);
   p = __builtin_fma(p, y, 0.02817013837425035);
-  p = __builtin_fma(p, y, 0.11640743724740873);
-  p = __builtin_fma(p, y, 0.3245623668173392);
-  p = __builtin_fma(p, y, 0.6971421572033232);
-  p = __builtin_fma(p, y, 1.214148030776356);
-  p = __builtin_fma(p, y, 1.7558051918274378);
+  p = __builtin_fma(p, y, 0.11640743724740872);
+  p = __builtin_fma(p, y, 0.324562366817339);
+  p = __builtin_fma(p, y, 0.6971421572033235);
+  p = __builtin_fma(p, y, 1.2141480307763557);
+  p = __builtin_fma(p, y, 1.7558051918274373);
   p = __builtin_fma(p, y, 2.129871446222046);
   return t * p;
 }
@@ -266,10 +268,11 @@ __device__ __forceinline__ void wave_order() {
 // no branch), 15 for one that is not; the form before took Phi through the
 // library's erfc on three branches of phi_diff, which the lanes of a wave
 // shared (600 instructions a sample).  A call of n = 1e6 x 256 ranges: 3.99
-// -> 0.85 ms.  Error of a single tail Q(z), on average and in 2^-53 of it: 2.0
-// for z < 1, 1.8 below 3, 4.1 below 6, 15 below 12, 65 below 25 (through erfc:
-// 0.8, 3.4, 14, 53, 227, nearly all of one sign); of COUNT and SUM in that call
-// 1.4e-16 before, 1.5e-16 now.
+// -> 0.85 ms.  Error of a single tail Q(z), on average and in 2^-53 of it: 1.9
+// for z < 1, 1.7 below 3, 4.2 below 6, 15 below 12, 65 below 25 (through erfc:
+// 0.8, 3.4, 14, 53, 227, nearly all of one sign); largest error of 30 calls'
+// COUNTs and SUMs in 2^-53 of the largest one, on average: 1.58 and 1.55
+// before, 1.44 and 1.54 now.
 template <bool FULL>
 __global__ __launch_bounds__(kThreads) void k_range_f64(const ColDesc* __restrict__ col, const double* __restrict__ lo,
                                                         const double* __restrict__ hi, double h, int piece_len,
@@ -328,15 +331,15 @@ __global__ __launch_bounds__(kThreads) void k_range_f64(const ColDesc* __restric
       evaluate(xq);
     }
   }
-  if (!FULL) {
-    if (lane < queued) evaluate(queue[wave][lane]);
-    if (lane == 0) cnt += (double)inside;
-  }
+  if (!FULL && lane < queued) evaluate(queue[wave][lane]);
+  __shared__ int whole[kThreads / 64];
+  if (lane == 0) whole[wave] = inside;
   __shared__ double sh[kThreads];
   cnt = block_sum_q(cnt, sh);
   sum = block_sum_q(sum, sh);
   if (threadIdx.x == 0) {
-    part[((int64_t)r * pieces + blockIdx.y) * 2] = cnt;
+    // the whole samples last: one rounding at their size
+    part[((int64_t)r * pieces + blockIdx.y) * 2] = cnt + (double)(whole[0] + whole[1] + whole[2] + whole[3]);
     part[((int64_t)r * pieces + blockIdx.y) * 2 + 1] = sum;
   }
 }

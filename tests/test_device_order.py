@@ -23,11 +23,11 @@ def test_range_queue_is_ordered_across_lanes(tmp_path):
     m = re.search(r"^\S*k_range_f64ILb0\S*:.*?\n(.*?)\.Lfunc_end", out.read_text(), re.M | re.S)
     assert m
     # up to the first block barrier, behind which the sums of the block follow
-    ops = re.findall(r"; wave barrier|\bds_write|\bds_read|\bs_barrier", m.group(1))
+    ops = re.findall(r"; wave barrier|\bds_write_b64|\bds_read_b64|\bs_barrier", m.group(1))
     ops = ops[:ops.index("s_barrier")]
-    stores = [k for k, o in enumerate(ops) if o == "ds_write"]
+    stores = [k for k, o in enumerate(ops) if o == "ds_write_b64"]
     # the queue's store, its load in the loop and the one after it; the last
     # store starts the block's sums
-    assert len(stores) == 2 and ops.count("ds_read") == 2
+    assert len(stores) == 2 and ops.count("ds_read_b64") == 2
     queue = ops[stores[0]:stores[1]]
-    assert queue == ["ds_write", "; wave barrier", "ds_read", "; wave barrier", "ds_read"]
+    assert queue == ["ds_write_b64", "; wave barrier", "ds_read_b64", "; wave barrier", "ds_read_b64"]
