@@ -351,11 +351,17 @@ void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<U
 // with).  Units a piece against whole ones, 100 bandwidths: 4 columns of n =
 // 3000 (1176 whole units, 9408 pieces) 0.42 and 0.38 ms, 8 of them 0.76 and
 // 0.69, 100 of them 8.9 and 7.5, 1000 of them 107 and 77; 40 of n = 1000
-// (1680, 13440) 0.97 and 0.93; at 16 of n = 1000 (672, 5376) both 0.43.
-constexpr size_t kWholeUnits = 1024, kSplitUnits = 6144;
-inline bool runs_whole(size_t units, size_t pieces) { return units >= kWholeUnits && pieces > kSplitUnits; }
+// (1680, 13440) 0.97 and 0.93; at 16 of n = 1000 (672, 5376) both 0.43.  A unit
+// of the FP64 form takes five times as long, so that its last round weighs more
+// and the host less: from 4096 on (20 columns of n = 1000, 1560 whole units,
+// 1.12 and 1.23 ms; 9 of n = 2000, 2340, 1.48 and 1.56; 4 of n = 4500, 4680,
+// both 2.71; 100 of n = 1000, 7800, 5.9 and 5.5).
+constexpr size_t kWholeUnits = 1024, kWholeUnits64 = 4096, kSplitUnits = 6144;
+inline bool runs_whole(size_t units, size_t pieces, bool f64) {
+  return units >= (f64 ? kWholeUnits64 : kWholeUnits) && pieces > kSplitUnits;
+}
 // Cuts a pass's whole LSCV units into a unit a piece where they are few.
-void split_lscv_units(IterPlan& it);
+void split_lscv_units(IterPlan& it, bool f64);
 void begin_stage(const ColPlan& p, int id, int stage, IterPlan& it);
 void lscv_rows_of(const ColPlan& p, const ColDesc& d, std::vector<RowDesc>& rows);
 void init_state(const ColPlan& p, double fp64_kappa, DevState& h);

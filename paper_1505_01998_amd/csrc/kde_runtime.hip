@@ -412,14 +412,14 @@ void lscv_units_of(const ColPlan& p, int id, std::vector<Unit>& u, std::vector<U
     }
 }
 
-void split_lscv_units(IterPlan& it) {
+void split_lscv_units(IterPlan& it, bool f64) {
   const auto step_of = [&](const Unit& w) {
     const int piece = it.cols[w.col].lscv_piece;
     return piece ? piece : w.j_end - w.j_begin;
   };
   size_t pieces = 0;
   for (const Unit& w : it.lscv_units) pieces += (w.j_end - w.j_begin) / step_of(w);
-  if (pieces == it.lscv_units.size() || runs_whole(it.lscv_units.size(), pieces)) return;
+  if (pieces == it.lscv_units.size() || runs_whole(it.lscv_units.size(), pieces, f64)) return;
   std::vector<Unit> u;
   std::vector<UnitCost> cost;
   for (size_t k = 0; k < it.lscv_units.size(); ++k) {
@@ -775,7 +775,7 @@ kde_status pack_pass(kde_ctx* c, IterPlan& it, PassLayout& L) {
     it.psi_narrow[q] = sort_psi_units(it.psi_units[q], it.psi_cost[q]);
     it.psi_cond_narrow[q] = sort_psi_units(it.psi_cond_units[q], it.psi_cond_cost[q]);
   }
-  if (it.lscv_whole) split_lscv_units(it);
+  if (it.lscv_whole) split_lscv_units(it, c->prec == KDE_PREC_FP64);
   sort_units(it.lscv_units, it.lscv_cost);
   if (lscv_queue_form(c, it)) {
     group_units(it.lscv_units, it.lscv_cost, it.cols, it.lscv_groups);
@@ -1183,7 +1183,7 @@ kde_status run_requests(kde_ctx* c, const kde_request* reqs, int32_t n_req, std:
       units += p.lscv_items.pairs.size() * p.n_chunks;
       pieces += p.lscv_items.pairs.size() * p.n_chunks * p.lscv_pieces;
     }
-  const bool whole = kde::runs_whole(units, pieces);
+  const bool whole = kde::runs_whole(units, pieces, c->prec == KDE_PREC_FP64);
   int extra = n_cols;  // tile pruning: two more descriptors per pruned column
   for (int k = 0; k < n_cols; ++k) {
     const kde::ColPlan& p = c->plans[k];

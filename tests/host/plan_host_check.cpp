@@ -98,42 +98,45 @@ int whole_units() {
     std::sort(k.begin(), k.end());
     return k;
   };
-  kde_ctx c;
-  for (int n : {2, 63, 64, 65, 256, 257, 511, 512, 513, 1000, 1025, 3001, 5003, 12345, 40001})
-    for (int n_h : {1, 16, 17, 100, 500})
-      for (int columns : {1, 3, 40, 700}) {
-        if ((double)n * columns > 1e6) continue;
-        const kde_request r = lscv_request(n, n_h);
-        kde::ColPlan p;
-        CHECK(kde::plan_column(&c, r, p).empty());
-        kde::ColDesc d;
-        kde::bind_column(p, (char*)4096, nullptr, nullptr, d);
-        CHECK(d.lscv_piece == (p.lscv_pieces > 1 ? kde::kBJ / p.lscv_pieces : 0));
-        kde::IterPlan it;
-        std::vector<kde::Unit> fine;
-        std::vector<kde::UnitCost> cost;
-        for (int k = 0; k < columns; ++k) {
-          it.cols.push_back(d);
-          kde::lscv_units_of(p, k, it.lscv_units, it.lscv_cost, true);
-          kde::lscv_units_of(p, k, fine, cost, false);
+  for (const bool f64 : {false, true}) {
+    kde_ctx c;
+    c.prec = f64 ? KDE_PREC_FP64 : KDE_PREC_MIXED;
+    for (int n : {2, 63, 64, 65, 256, 257, 511, 512, 513, 1000, 1025, 3001, 5003, 12345, 40001})
+      for (int n_h : {1, 16, 17, 100, 500})
+        for (int columns : {1, 3, 40, 700}) {
+          if ((double)n * columns > 1e6) continue;
+          const kde_request r = lscv_request(n, n_h);
+          kde::ColPlan p;
+          CHECK(kde::plan_column(&c, r, p).empty());
+          kde::ColDesc d;
+          kde::bind_column(p, (char*)4096, nullptr, nullptr, d);
+          CHECK(d.lscv_piece == (p.lscv_pieces > 1 ? kde::kBJ / p.lscv_pieces : 0));
+          kde::IterPlan it;
+          std::vector<kde::Unit> fine;
+          std::vector<kde::UnitCost> cost;
+          for (int k = 0; k < columns; ++k) {
+            it.cols.push_back(d);
+            kde::lscv_units_of(p, k, it.lscv_units, it.lscv_cost, true);
+            kde::lscv_units_of(p, k, fine, cost, false);
+          }
+          const size_t whole = it.lscv_units.size();
+          CHECK(whole * p.lscv_pieces == fine.size());
+          kde::split_lscv_units(it, f64);
+          if (whole >= (f64 ? 4096u : 1024u) && fine.size() > 6144) {
+            CHECK(it.lscv_units.size() == whole);
+            // every slot of every item, once
+            std::vector<int> seen((size_t)columns * d.n_items, 0);
+            for (const kde::Unit& u : it.lscv_units)
+              if (u.chunk == 0)
+                for (int q = 0; q < p.lscv_pieces; ++q) ++seen[(size_t)u.col * d.n_items + u.item + q];
+            for (int s : seen) CHECK(s == 1);
+          } else {
+            CHECK(keys(it.lscv_units, it.lscv_cost) == keys(fine, cost));
+          }
+          // a single column always fills the chip with its pieces
+          CHECK(columns > 1 || it.lscv_units.size() == fine.size());
         }
-        const size_t whole = it.lscv_units.size();
-        CHECK(whole * p.lscv_pieces == fine.size());
-        kde::split_lscv_units(it);
-        if (whole >= kde::kWholeUnits && fine.size() > kde::kSplitUnits) {
-          CHECK(it.lscv_units.size() == whole);
-          // every slot of every item, once
-          std::vector<int> seen((size_t)columns * d.n_items, 0);
-          for (const kde::Unit& u : it.lscv_units)
-            if (u.chunk == 0)
-              for (int q = 0; q < p.lscv_pieces; ++q) ++seen[(size_t)u.col * d.n_items + u.item + q];
-          for (int s : seen) CHECK(s == 1);
-        } else {
-          CHECK(keys(it.lscv_units, it.lscv_cost) == keys(fine, cost));
-        }
-        // a single column always fills the chip with its pieces
-        CHECK(columns > 1 || it.lscv_units.size() == fine.size());
-      }
+  }
   return 0;
 }
 

@@ -21,7 +21,8 @@ _SIZES = (2, 63, 65, 200, 256, 257, 300, 511, 512, 513, 700, 1000, 1025)
 def test_columns_of_a_large_batch_are_those_alone(precision, options):
     import paper_1505_01998_amd as kde
 
-    # 1600 (of 32 bandwidths) to 6500 (of 8) whole units; from 1024 on, with over 6144 pieces, they run whole
+    # 1800 (of 32 bandwidths) to 6700 (of 8) whole units; from 1024 on (FP64:
+    # 4096), with over 6144 pieces, they run whole
     reqs = [kde.Request(workloads.draw("bimodal", n, 7 * n + k, np.float32), kde.KDE_METHOD_LSCV, 2,
                         ("log_rot", 0.1, 2.0, 60 + 13 * k)) for k in range(12) for n in _SIZES]
     with kde.Context(0, precision) as c:
