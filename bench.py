@@ -73,9 +73,9 @@ TRAFFIC_SOURCES = ("kde_internal.h", "kde_kernels.hip", "kde_runtime.hip")
 MEASURED_TRAFFIC = {
     "workload": "lognormal-1m",
     "kernel": "k_lscv_units_f32_queue<16, 512>",
-    "sources_sha256": "0041dd2360dfddef8adc54ede717e54a337c78ad02dce0be015dce3f1b4edf47",
-    "fetch_bytes": 1.68762e+08,
-    "write_bytes": 1.14259e+09,
+    "sources_sha256": "d8df86cf046833cd6e5078349444e4b835734a3fc11bf5cd6b5a83ee39019bfb",
+    "fetch_bytes": 1.70794e+08,
+    "write_bytes": 1.14789e+09,
 }
 
 
